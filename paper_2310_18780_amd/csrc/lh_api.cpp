@@ -184,6 +184,14 @@ lh_status check_prefill_buffers(const lh_c32* lambda, const lh_c32* R, const flo
     return LH_OK;
 }
 
+// A scan runs on the matrix cores where its sizes allow; with less workspace than
+// their tables need it runs on the VALU, as with exactly the VALU scan's size.
+void use_scan(lh::PrefillPlan* p)
+{
+    p->mfma = false;
+    p->ws_bytes = p->scan_bytes;
+}
+
 // ---- static scratch of lh_prefill_noalloc
 //
 // Device memory that the library itself holds: one array per GPU the
@@ -265,7 +273,7 @@ int lh_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t plan, lh
         return -1;
     lh::PrefillPlan p;
     if (!lh::make_prefill_plan(B, D, d, T, plan, io_dtype == LH_BF16 ? 1 : 0, &p)) return -1;
-    return p.mfma_seg ? LH_PLAN_MFMA_SEG : p.mfma ? LH_PLAN_MFMA : LH_PLAN_SCAN;
+    return p.named;
 }
 
 lh_status lh_prefill_with_plan(const lh_c32* lambda, const lh_c32* R, const float* h0,
@@ -293,10 +301,11 @@ lh_status lh_prefill_with_plan(const lh_c32* lambda, const lh_c32* R, const floa
                         ? " (the segmented matrix-core plan also needs T = s * 2^k * 32 "
                           "steps, k >= 1, segments of at least 256 steps)"
                         : "");
-    if (pl.mfma_forced && (reinterpret_cast<uintptr_t>(u) % 16 != 0 ||
+    if (pl.forced && (reinterpret_cast<uintptr_t>(u) % 16 != 0 ||
                            reinterpret_cast<uintptr_t>(y) % 16 != 0))
         return fail(LH_ERR_INVALID_ARG, "the matrix-core plan needs 16-byte aligned u and y");
 
+    if (pl.named == LH_PLAN_SCAN && workspace_bytes < pl.ws_bytes) use_scan(&pl);
     if ((s = check_prefill_buffers(lambda, R, h0, u, B, D, d, T, io_dtype, state, y, workspace,
                                    pl.ws_bytes, workspace_bytes)) != LH_OK)
         return s;
@@ -332,6 +341,7 @@ lh_status lh_prefill_noalloc(const lh_c32* lambda, const lh_c32* R, const float*
     lh::PrefillPlan pl;
     if (!lh::make_prefill_plan(B, D, d, T, LH_PREFILL_AUTO, io_dtype == LH_BF16 ? 1 : 0, &pl))
         return fail(LH_ERR_INVALID_ARG, "no prefill plan for these sizes");
+    if (pl.named == LH_PLAN_SCAN && pl.ws_bytes > kScratchBytes) use_scan(&pl);
     if (pl.ws_bytes > kScratchBytes)
         return fail(LH_ERR_WORKSPACE,
                     "these sizes need %zu bytes of scratch; the static scratch of "

@@ -31,24 +31,30 @@ __device__ __forceinline__ void io_store_nt(bf16* p, float v) {
     __builtin_nontemporal_store(__builtin_bit_cast(uint16_t, static_cast<__bf16>(v)), &p->bits);
 }
 
+// Columns and segments of a matrix-core prefill.
+struct MfmaCut {
+    int s;            // time chunks per row among the kernel's 16 columns (2, 4 or 16)
+    int nseg;         // segments of the prompt (1: the whole prompt in one pass)
+    int64_t seg_len;  // steps per segment (a multiple of 256 when nseg > 1)
+    int64_t tiles;    // estimated time, in tiles of the busiest CU
+};
+
 // How the prefill of one call is cut up.
 struct PrefillPlan {
     int lpr;          // lanes per (b, c) row: the modes of a row are split over lpr lanes
     int mpl;          // modes per lane (power of two <= 16); lpr * mpl >= d
-    int64_t C;        // chunk length (time steps per chunk)
+    int64_t C;        // VALU chunk length (time steps per chunk)
     int64_t nchunks;  // ceil(T / C); 0 when T == 0
     size_t off_pow;   // workspace offset of lambda^C          [D, d] complex64
-    size_t off_xin;   // workspace offset of chunk entry states [B, nchunks, D, d] complex64
-    size_t ws_bytes;  // total workspace bytes (0 when nchunks <= 1 and no MFMA plan)
-    bool mfma;        // matrix-core prefill (automatic plans use it when u and y are
-                      // 16-byte aligned, else the VALU plan above)
-    bool mfma_forced; // requested explicitly: u and y must be 16-byte aligned
-    bool mfma_seg;    // segmented matrix-core plan: the prompt is cut into nchunks
-                      // segments of C steps (C % 32 == 0, T == nchunks C); state pass
-                      // and output pass on the matrix cores, carry in between (falls
-                      // back to the VALU chunked scan with the same C when u or y is
-                      // not 16-byte aligned)
-    size_t off_mfma;  // workspace offset of the matrix-core tables (segmented plan)
+    size_t off_xin;   // workspace offset of chunk (segment) entry states [B, n, D, d] complex64
+    size_t ws_bytes;  // total workspace bytes
+    size_t scan_bytes;  // workspace of the VALU scan (a plan that is reported as a scan
+                        // takes it when the workspace holds no more)
+    int named;        // reported plan: 0 scan, 1 matrix cores, 2 segmented matrix cores
+    bool mfma;        // runs on the matrix cores, cut as `cut`
+    bool forced;      // a matrix-core plan was requested: u and y must be 16-byte aligned
+    MfmaCut cut;
+    size_t off_mfma;  // workspace offset of the matrix-core tables
 };
 
 // The plan of a prefill call.  request: 0 automatic, > 0 the VALU chunked
@@ -66,35 +72,29 @@ hipError_t launch_prefill(const float2* lam, const float2* R, const float* h0,
                           int64_t T, float2* state, void* y, const PrefillPlan& plan,
                           void* workspace, hipStream_t stream);
 
-// Matrix-core prefill: d = 16 or 32 with D a multiple of 8 (bfloat16
-// operands), or d = 64 with float32 u/y and D a multiple of 4 (float32
-// operands).
+// Matrix-core prefill.  Sizes that the explicit matrix-core requests take (d = 16
+// or 32 with D a multiple of 8, or d = 64 with float32 u/y and D a multiple of 4),
+// and sizes that the kernel takes.
 bool mfma_supported(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io);
-// Whether the automatic plan takes the whole-prompt matrix-core plan over the
-// segmented one.
-bool mfma_preferred(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io);
-// The automatic plan where the matrix-core plans are supported: 0 the VALU
-// scan, 1 the whole-prompt matrix-core plan, 2 the segmented one.
-int mfma_auto_plan(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io);
+bool mfma_possible(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io);
+// Table bytes of the named plans (either input type) and of one input type.
 size_t mfma_workspace_bytes(int64_t D, int64_t d);
-// Segment count of the segmented matrix-core plan (0 when T does not split
-// into segments of a multiple of 32 steps, at least 256 long).
+size_t mfma_table_bytes(bool bf16_io, int64_t D, int64_t d);
+// Segment slots of the segmented plan's workspace (0 when T does not split into
+// segments of a multiple of 32 steps, at least 256 long).
 int64_t mfma_segments(int64_t B, int64_t D, int64_t d, int64_t T);
-// Matrix-core tables of the filters into the workspace (bf16_io: only the
-// operand terms the bfloat16 kernels read are written).
+// The cut of a call into columns and at most max_seg segments.
+MfmaCut mfma_cut(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64_t max_seg);
+// Tables of the filters into the workspace.
 hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0, int64_t D,
                              int64_t d, bool bf16_io, void* workspace, hipStream_t stream);
-// One pass of the segmented plan: outputs = false writes each segment's end
-// state from zero into slot k < nseg - 1 of xs [B, nseg, D, d]; outputs = true
-// runs every segment from its entry state in xs, writes y and x_T.
-hipError_t launch_mfma_segment_pass(bool outputs, const float2* lam, const void* u,
-                                    bool bf16_io, int64_t B, int64_t D, int64_t d, int64_t T,
-                                    int nseg, int64_t seg_len, float2* xs, float2* state,
-                                    void* y, const void* workspace, hipStream_t stream);
-hipError_t launch_prefill_mfma(const float2* lam, const float2* R, const float* h0,
-                               const void* u, bool bf16_io, int64_t B, int64_t D, int64_t d,
-                               int64_t T, float2* state, void* y, void* workspace,
-                               hipStream_t stream);
+// One pass: outputs = false writes each segment's end state from zero into slot
+// k < nseg - 1 of xs [B, nseg, D, d]; outputs = true runs every segment from its
+// entry state in xs (the whole prompt from zero when nseg = 1), writes y and x_T.
+hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool bf16_io,
+                            int64_t B, int64_t D, int64_t d, int64_t T, const MfmaCut& cut,
+                            float2* xs, float2* state, void* y, const void* workspace,
+                            hipStream_t stream);
 
 hipError_t launch_step(const float2* lam, const float2* R, const float* h0, float2* state,
                        const void* u_t, void* y_t, bool bf16_io, int64_t B, int64_t D,

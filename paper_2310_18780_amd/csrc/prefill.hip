@@ -25,6 +25,8 @@
 // butterfly over lanes CW apart.  Inputs are prefetched kPf steps ahead; the
 // main loop carries no bounds checks (the channel index is clamped for lanes
 // past D, whose results are discarded), a short tail loop finishes the chunk.
+#include <algorithm>
+
 #include "lh_internal.hpp"
 
 namespace lh {
@@ -287,6 +289,42 @@ inline bool grid_for(int64_t n, dim3* g)
 
 }  // namespace
 
+namespace {
+
+constexpr int64_t kMaxSegments = 64;
+
+// The named plan of an automatic call at sizes that the explicit requests take:
+// the whole prompt where its (channel, row) tiles fill the GPU or there are 16
+// rows and more, the segmented plan for fewer rows of a prompt that splits; at
+// d = 64 also the whole prompt from 4 rows on.
+int named_auto(int64_t B, int64_t D, int64_t d, int64_t T, int64_t slots)
+{
+    if (d == 64 && B < 4 && B * T <= 1024) return 0;
+    if ((D + 15) / 16 * ((B + 31) / 32) >= 256) return 1;
+    if (slots >= 2) return B >= 16 ? 1 : 2;
+    return d == 64 && B >= 4 ? 1 : 0;
+}
+
+// Whether sizes that no explicit request names run faster on the matrix cores
+// than in the VALU scan p, by estimates in nanoseconds fitted to both (62 shapes, B =
+// 1..300, D = 64..4096, d = 4..63, T = 16..16384, both types; the choice then cost
+// 3% and 12% at two of them).  Matrix cores: tables and launches, then 2.3 us (bfloat16)
+// or 2.6 us (float32) per tile.  Scan: 0.26 ps per element and padded mode in one
+// pass, 0.42 ps in chunks (two passes), but no less than its memory time, and 30 ns
+// per step of one pass, or the launches and 250 ns per chunk of the carry.
+bool mfma_faster(int64_t B, int64_t D, int64_t T, bool bf16_io, const PrefillPlan& p)
+{
+    const double el = double(B) * double(T) * double(D), modes = double(p.lpr) * p.mpl;
+    const double mem = el * (bf16_io ? 4 : 8) / 4000.0;
+    const double mfma = 13e3 + double(p.cut.tiles) * (bf16_io ? 2300.0 : 2600.0);
+    const double scan = p.nchunks <= 1
+                            ? 9e3 + 30.0 * double(T) + std::max(el * modes * 0.26e-3, mem)
+                            : 20e3 + 250.0 * double(p.nchunks) + std::max(el * modes * 0.42e-3, 1.5 * mem);
+    return mfma < scan;
+}
+
+}  // namespace
+
 bool make_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t request, int io,
                        PrefillPlan* plan)
 {
@@ -340,47 +378,51 @@ bool make_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t reque
         }
         p.nchunks = (T + p.C - 1) / p.C;
     }
-    p.ws_bytes = 0;
     p.off_pow = 0;
     p.off_xin = 0;
-    if (p.nchunks > 1) {
-        const size_t pow_bytes = static_cast<size_t>(D) * d * sizeof(float2);
-        p.off_xin = (pow_bytes + 255) / 256 * 256;
-        p.ws_bytes = p.off_xin + static_cast<size_t>(B) * p.nchunks * D * d * sizeof(float2);
-    }
-    // The automatic plan runs on the matrix cores where supported; the
-    // workspace also covers the VALU plan above, taken when u or y is not
-    // 16-byte aligned.
-    p.mfma_forced = request == -1 || request == -2;
-    if (p.mfma_forced && !mfma_supported(B, D, d, T, io == 1)) return false;
-    const int choice = request == 0 && mfma_supported(B, D, d, T, io == 1)
-                           ? mfma_auto_plan(B, D, d, T, io == 1)
-                           : 0;
-    p.mfma = request == -1 || choice == 1;
-    p.mfma_seg = false;
-    p.off_mfma = 0;
-    if (p.mfma) {
+    const size_t pow_bytes = static_cast<size_t>(D) * d * sizeof(float2);
+    p.off_xin = (pow_bytes + 255) / 256 * 256;
+    p.scan_bytes = 0;
+    if (p.nchunks > 1)
+        p.scan_bytes = p.off_xin + static_cast<size_t>(B) * p.nchunks * D * d * sizeof(float2);
+    p.ws_bytes = p.scan_bytes;
+
+    // matrix cores
+    p.forced = request == -1 || request == -2;
+    const bool bf = io == 1;
+    const bool supported = mfma_supported(B, D, d, T, bf);
+    const int64_t slots = supported ? mfma_segments(B, D, d, T) : 0;
+    if (p.forced && (!supported || (request == -2 && slots < 2))) return false;
+    p.named = p.forced ? -static_cast<int>(request)
+              : request == 0 && supported ? named_auto(B, D, d, T, slots)
+                                          : 0;
+    const bool possible = mfma_possible(B, D, d, T, bf);
+    if (p.named == 1) {
+        p.mfma = possible;
+        p.cut = mfma_cut(B, D, d, T, bf, 1);
         const size_t mb = mfma_workspace_bytes(D, d);
-        if (p.mfma_forced || mb > p.ws_bytes) p.ws_bytes = mb;  // a forced plan has no fallback
-    } else if (request == -2 || choice == 2) {
-        // too few (batch row, channel group) tiles for the whole-prompt matrix-core
-        // plan: cut the prompt into segments that run in parallel, on the matrix
-        // cores, with the chunked scan's carry in between
-        const int64_t nseg = mfma_segments(B, D, d, T);
-        if (nseg >= 2) {
-            p.mfma_seg = true;
-            p.C = T / nseg;
-            p.nchunks = nseg;
-            const size_t pow_bytes = static_cast<size_t>(D) * d * sizeof(float2);
-            p.off_pow = 0;
-            p.off_xin = (pow_bytes + 255) / 256 * 256;
-            const size_t xin_bytes = static_cast<size_t>(B) * nseg * D * d * sizeof(float2);
-            p.off_mfma = (p.off_xin + xin_bytes + 255) / 256 * 256;
-            p.ws_bytes = p.off_mfma + mfma_workspace_bytes(D, d);
-        } else if (request == -2) {
-            return false;
+        if (p.forced || mb > p.ws_bytes) p.ws_bytes = mb;
+    } else if (p.named == 2) {
+        p.mfma = possible;
+        p.cut = mfma_cut(B, D, d, T, bf, slots);
+        const size_t xin_bytes = static_cast<size_t>(B) * slots * D * d * sizeof(float2);
+        p.off_mfma = (p.off_xin + xin_bytes + 255) / 256 * 256;
+        p.ws_bytes = p.off_mfma + mfma_workspace_bytes(D, d);
+    } else if (request == 0 && possible) {
+        // any other size: the same kernel where it is the faster one
+        p.cut = mfma_cut(B, D, d, T, bf, kMaxSegments);
+        if (mfma_faster(B, D, T, bf, p)) {
+            p.mfma = true;
+            size_t off = 0;
+            if (p.cut.nseg > 1)
+                off = (p.off_xin + static_cast<size_t>(B) * p.cut.nseg * D * d * sizeof(float2) + 255) /
+                      256 * 256;
+            p.off_mfma = off;
+            const size_t mb = off + mfma_table_bytes(bf, D, d);
+            if (mb > p.ws_bytes) p.ws_bytes = mb;
         }
     }
+    if (!p.mfma && p.ws_bytes < p.scan_bytes) p.ws_bytes = p.scan_bytes;
     *plan = p;
     return true;
 }
@@ -398,28 +440,25 @@ hipError_t launch_prefill(const float2* lam, const float2* R, const float* h0, c
         hipLaunchKernelGGL(zero_kernel, g_state, dim3(kBlock), 0, stream, state, B * D * d);
         return hipGetLastError();
     }
-    const bool aligned16 = reinterpret_cast<uintptr_t>(u) % 16 == 0 &&
-                           reinterpret_cast<uintptr_t>(y) % 16 == 0;
-    if (p.mfma && aligned16)
-        return launch_prefill_mfma(lam, R, h0, u, bf16_io, B, D, d, T, state, y, workspace,
-                                   stream);
-    if (p.mfma_seg && aligned16) {
+    if (p.mfma) {
         char* ws = static_cast<char*>(workspace);
         float2* lamC = reinterpret_cast<float2*>(ws + p.off_pow);
         float2* xs = reinterpret_cast<float2*>(ws + p.off_xin);
         void* mws = ws + p.off_mfma;
         hipError_t e;
-        hipLaunchKernelGGL(pow_kernel, g_pow, dim3(kBlock), 0, stream, lam, lamC, D * d, p.C);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = launch_mfma_setup(lam, R, h0, D, d, bf16_io, mws, stream)) != hipSuccess) return e;
-        if ((e = launch_mfma_segment_pass(false, lam, u, bf16_io, B, D, d, T, int(p.nchunks), p.C,
-                                          xs, state, y, mws, stream)) != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(carry_kernel, g_state, dim3(kBlock), 0, stream, lamC, xs, B, D * d,
-                           p.nchunks);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        return launch_mfma_segment_pass(true, lam, u, bf16_io, B, D, d, T, int(p.nchunks), p.C,
-                                        xs, state, y, mws, stream);
+        if (p.cut.nseg > 1) {
+            hipLaunchKernelGGL(pow_kernel, g_pow, dim3(kBlock), 0, stream, lam, lamC, D * d,
+                               p.cut.seg_len);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            if ((e = launch_mfma_pass(false, lam, u, bf16_io, B, D, d, T, p.cut, xs, state, y, mws,
+                                      stream)) != hipSuccess)
+                return e;
+            hipLaunchKernelGGL(carry_kernel, g_state, dim3(kBlock), 0, stream, lamC, xs, B, D * d,
+                               int64_t(p.cut.nseg));
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+        return launch_mfma_pass(true, lam, u, bf16_io, B, D, d, T, p.cut, xs, state, y, mws, stream);
     }
     float2* lamC = nullptr;
     float2* xs = nullptr;

@@ -1,0 +1,140 @@
+"""The matrix-core prefill at sizes that only the automatic choice takes (any
+order up to 64, any width and prompt length), at the edges of its tilings: 1, 2, 4
+and 16 time chunks per row among the kernel's columns, segments with a shorter
+last one, partial chunks and tiles, ragged rows, widths that leave a partial
+channel group or an unaligned row, and the smallest widths.
+
+Compared over every output and state with the VALU scan in one sequential pass
+(another kernel, another association of the sums).  Both are within 1e-4 of the
+exact result, relative to the largest value of the (b, c) row (checked against the
+oracle elsewhere, here on two rows), so they differ by at most twice that; bfloat16
+outputs by one rounding on each side more.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from parity_util import BF16_REL, REL_TOL, to_device
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (B, D, d, T, io); chunks per row among the columns by the rule of the cut
+    (60, 1022, 12, 100, "f32"),   # 1: partial chunk, D % 16 != 0, ragged rows
+    (50, 2035, 7, 83, "bf16"),    # 1: D odd
+    (33, 1100, 30, 95, "f32"),    # 1, two sixteens of modes
+    (45, 1030, 24, 70, "bf16"),   # 1
+    (17, 1203, 45, 66, "f32"),    # 2: three sixteens
+    (40, 600, 60, 130, "bf16"),   # 1: four sixteens
+    (19, 530, 61, 71, "f32"),     # 2
+    (9, 1030, 12, 250, "f32"),    # 4
+    (23, 1500, 16, 301, "bf16"),  # 2
+    (12, 700, 20, 520, "f32"),    # 4
+    (5, 530, 40, 333, "bf16"),    # 4
+    (3, 101, 5, 1000, "f32"),     # 16
+    (2, 36, 48, 257, "f32"),
+    (1, 64, 12, 16 * 1024 + 9, "f32"),   # segments, the last one partial
+    (2, 72, 17, 8192 + 256, "bf16"),     # segments, the last one of one tile
+    (1, 24, 33, 5000, "f32"),
+    (6, 4, 64, 300, "bf16"),      # one piece of channels
+    (300, 18, 33, 200, "f32"),    # half a channel group, whole pieces
+]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+
+    import paper_2310_18780_amd as lh
+
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    lh.lib()
+    yield
+
+
+def _inputs(B, D, d, T, io, seed):
+    import torch
+
+    w = workloads.Workload("case", B, D, d, T, 0, io, 0.7, 0.9999, np.pi, 1.0 / d, seed)
+    lam, R, h0 = workloads.make_params(w)
+    t = to_device(lam, R, h0, np.zeros((1, 1, D), np.float32), np.zeros((1, 0, D), np.float32), "f32")
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    u = torch.randn((B, T, D), generator=g, device="cuda").to(
+        torch.bfloat16 if io == "bf16" else torch.float32)
+    return (lam, R, h0), t, u
+
+
+def _run(call, u, d):
+    import torch
+
+    B, T, D = u.shape
+    y = torch.full_like(u, float("nan"))
+    x = torch.full((B, D, d), complex(float("nan"), 0), dtype=torch.complex64, device="cuda")
+    call(x, y)
+    torch.cuda.synchronize()
+    return y, x
+
+
+def _same(a, b, io):
+    """Outputs and states of two plans within twice the row tolerance."""
+    (ya, xa), (yb, xb) = a, b
+    err = (ya.float() - yb.float()).abs()
+    bound = 2 * REL_TOL * yb.float().abs().amax(dim=1, keepdim=True)
+    if io == "bf16":
+        bound = bound + 2 * BF16_REL * yb.float().abs()
+    assert bool((err <= bound).all()), float((err - bound).max())
+    xerr = (xa - xb).abs()
+    assert bool((xerr <= 2 * REL_TOL * xb.abs().amax(dim=2, keepdim=True)).all())
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "B%d_D%d_d%d_T%d_%s" % c)
+def test_against_the_scan(case):
+    import paper_2310_18780_amd as lh
+
+    B, D, d, T, io = case
+    (lam, R, h0), t, u = _inputs(*case, seed=B * 1000 + d)
+    print(f"[columns] {case}", flush=True)
+    auto = _run(lambda x, y: lh.prefill(t["lam"], t["R"], t["h0"], u, x, y), u, d)
+    scan = _run(lambda x, y: lh.prefill_with_plan(t["lam"], t["R"], t["h0"], u, x, y, T), u, d)
+    _same(auto, scan, io)
+    rows = [(B - 1, D - 1), (B // 2, D // 3)]
+    up = u.float().cpu().numpy()
+    ref = oracle.run_rows(lam, R, h0, up, np.zeros((B, 0, D), np.float32), rows)
+    for i, (b, c) in enumerate(rows):
+        y, x = auto[0][b, :, c].float().cpu().numpy(), auto[1][b, c].cpu().numpy()
+        e = np.abs(y - ref["y_prefill"][i])
+        tol = REL_TOL * np.abs(ref["y_prefill"][i]).max()
+        assert np.all(e <= tol + (BF16_REL * np.abs(ref["y_prefill"][i]) if io == "bf16" else 0))
+        assert np.abs(x - ref["x_T"][i]).max() <= REL_TOL * np.abs(ref["x_T"][i]).max()
+
+
+def test_scratch_limits():
+    """With less scratch than the tables need a call runs the VALU scan: a
+    workspace of exactly the scan's size, and lh_prefill_noalloc past its 64 MiB."""
+    import torch
+
+    import paper_2310_18780_amd as lh
+
+    B, D, d, T = 3, 200, 12, 700
+    _, t, u = _inputs(B, D, d, T, "f32", 5)
+    args = (t["lam"], t["R"], t["h0"], u)
+    cut = 64  # the automatic scan's chunk: 3 x 4 waves, 64 steps each
+    need = lh.workspace_bytes(B, D, d, T, plan=cut)
+    assert need < lh.workspace_bytes(B, D, d, T)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    small = _run(lambda x, y: lh.prefill(*args, x, y, workspace=ws), u, d)
+    scan = _run(lambda x, y: lh.prefill_with_plan(*args, x, y, cut), u, d)
+    assert torch.equal(small[0], scan[0]) and torch.equal(small[1], scan[1])
+    with pytest.raises(lh.LHError):
+        lh.prefill(*args, small[1], small[0], workspace=ws[:-256])
+
+    B, D, d, T = 16, 2560, 60, 70  # 77 MB of tables; the scan is one pass
+    _, t, u = _inputs(B, D, d, T, "f32", 6)
+    args = (t["lam"], t["R"], t["h0"], u)
+    assert lh.workspace_bytes(B, D, d, T) > lh.NOALLOC_SCRATCH_BYTES
+    held = _run(lambda x, y: lh.prefill_noalloc(*args, x, y), u, d)
+    scan = _run(lambda x, y: lh.prefill_with_plan(*args, x, y, T), u, d)
+    assert torch.equal(held[0], scan[0]) and torch.equal(held[1], scan[1])
