@@ -306,20 +306,25 @@ int named_auto(int64_t B, int64_t D, int64_t d, int64_t T, int64_t slots)
 }
 
 // Whether sizes that no explicit request names run faster on the matrix cores
-// than in the VALU scan p, by estimates in nanoseconds fitted to both (62 shapes, B =
-// 1..300, D = 64..4096, d = 4..63, T = 16..16384, both types; the choice then cost
-// 3% and 12% at two of them).  Matrix cores: tables and launches, then 2.3 us (bfloat16)
-// or 2.6 us (float32) per tile.  Scan: 0.26 ps per element and padded mode in one
-// pass, 0.42 ps in chunks (two passes), but no less than its memory time, and 30 ns
-// per step of one pass, or the launches and 250 ns per chunk of the carry.
-bool mfma_faster(int64_t B, int64_t D, int64_t T, bool bf16_io, const PrefillPlan& p)
+// than in the VALU scan p, by estimates in nanoseconds whose constants were fitted to
+// the times of both at 174 shapes (B = 1..300, D = 64..4096, d = 4..63, T =
+// 16..16384, both types).  Matrix cores: launches, the tables of D channels, then
+// the tiles of the busiest CU.  Scan: launches, latency per step (the modes of a
+// lane one after the other), then the arithmetic per element and padded mode or
+// the memory traffic; in chunks two passes and a carry that walks the chunks.  At
+// these shapes the choice is never more than 3% slower than the scan, and up to
+// 4.2 times as fast; it misses the matrix cores at six where they are 4-36% faster.
+bool mfma_faster(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, const PrefillPlan& p)
 {
     const double el = double(B) * double(T) * double(D), modes = double(p.lpr) * p.mpl;
     const double mem = el * (bf16_io ? 4 : 8) / 4000.0;
-    const double mfma = 13e3 + double(p.cut.tiles) * (bf16_io ? 2300.0 : 2600.0);
-    const double scan = p.nchunks <= 1
-                            ? 9e3 + 30.0 * double(T) + std::max(el * modes * 0.26e-3, mem)
-                            : 20e3 + 250.0 * double(p.nchunks) + std::max(el * modes * 0.42e-3, 1.5 * mem);
+    const double mfma = 13000 + 1.8 * double(D) * double((d + 15) / 16) +
+                        double(p.cut.tiles) * (bf16_io ? 3400 : 3200);
+    const double scan =
+        p.nchunks <= 1
+            ? 11400 + (36 + 1.8 * modes) * double(T) + std::max(0.32e-3 * el * modes, mem)
+            : 24200 + 480 * double(p.nchunks) + 3.6 * modes * double(p.C) +
+                  std::max(0.35e-3 * el * modes, 1.7 * mem);
     return mfma < scan;
 }
 
@@ -411,15 +416,14 @@ bool make_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t reque
     } else if (request == 0 && possible) {
         // any other size: the same kernel where it is the faster one
         p.cut = mfma_cut(B, D, d, T, bf, kMaxSegments);
-        if (mfma_faster(B, D, T, bf, p)) {
+        if (mfma_faster(B, D, d, T, bf, p)) {
             p.mfma = true;
             size_t off = 0;
             if (p.cut.nseg > 1)
                 off = (p.off_xin + static_cast<size_t>(B) * p.cut.nseg * D * d * sizeof(float2) + 255) /
                       256 * 256;
             p.off_mfma = off;
-            const size_t mb = off + mfma_table_bytes(bf, D, d);
-            if (mb > p.ws_bytes) p.ws_bytes = mb;
+            p.ws_bytes = off + mfma_table_bytes(bf, D, d);
         }
     }
     if (!p.mfma && p.ws_bytes < p.scan_bytes) p.ws_bytes = p.scan_bytes;

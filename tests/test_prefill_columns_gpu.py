@@ -92,6 +92,8 @@ def _same(a, b, io):
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "B%d_D%d_d%d_T%d_%s" % c)
 def test_against_the_scan(case):
+    import torch
+
     import paper_2310_18780_amd as lh
 
     B, D, d, T, io = case
@@ -99,6 +101,7 @@ def test_against_the_scan(case):
     print(f"[columns] {case}", flush=True)
     auto = _run(lambda x, y: lh.prefill(t["lam"], t["R"], t["h0"], u, x, y), u, d)
     scan = _run(lambda x, y: lh.prefill_with_plan(t["lam"], t["R"], t["h0"], u, x, y, T), u, d)
+    assert not torch.equal(auto[1], scan[1])  # the automatic choice is not the scan
     _same(auto, scan, io)
     rows = [(B - 1, D - 1), (B // 2, D // 3)]
     up = u.float().cpu().numpy()
