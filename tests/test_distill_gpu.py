@@ -139,3 +139,20 @@ def test_without_filter_output_and_determinism():
     for k in ("loss", "dA", "dtheta"):
         assert np.array_equal(a[k].view(np.uint32), b[k].view(np.uint32)), k
     assert np.array_equal(a["dR"].view(np.uint64), b["dR"].view(np.uint64))
+
+
+@pytest.mark.parametrize("case", [
+    (3, 16, 255), (2, 17, 256), (2, 33, 257),   # around one 256-tap tile, each count of sixteen modes
+    (1, 48, 1023), (1, 64, 1025),               # one tile per wave, and one more
+    (1, 64, 8192), (2, 5, 8193),                # around the 32 tiles whose powers are held at a time
+    (1, 20, 16400),                             # three such blocks, the last of one ragged tile
+    (2, 65, 513),                               # past 64 modes: the VALU kernel
+], ids=str)
+def test_tile_edges(case):
+    D, d, L = case
+    _log(f"distill edge {case}")
+    (A, th, R), w = params(D, d, seed=11)
+    A = A.copy()
+    A[0, 0] = 0.0
+    tgt = workloads.distill_target(w, L, tau=max(8.0, L / 8))
+    compare(run_gpu(A, th, R, tgt), od.distill_loss_grad(A, th, R, tgt), str(case))
