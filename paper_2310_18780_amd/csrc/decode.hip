@@ -8,20 +8,24 @@
 // kernel is bound by memory bandwidth (16 bytes of state traffic per mode
 // against 12 flops).
 //
-// Fast path (d even, d/2 a power of two <= 64, 16-byte aligned arrays): the
-// d/2 mode pairs of a (b, c) row sit on LPR = d/2 consecutive lanes, one
-// 16-byte access each, so a wavefront reads and writes one contiguous span
-// of the state; the row sum is a butterfly over those lanes (DPP within 16
-// lanes).  Each thread serves NB batch rows of the same (c, mode pair):
-// lambda and R are loaded once for the NB rows, and every thread has NB
-// independent 16-byte state loads in flight before it computes.  NB = 8
+// Lanes path (d even up to 128 in 16-byte aligned arrays, else d up to 64): the
+// modes of a (b, c) row sit two (one) to a lane on LPR consecutive lanes, LPR the
+// power of two that holds them, one 16-byte (8-byte) access each; lanes past d hold
+// zeros, so any order reads and writes contiguous spans of the state.  (Against the
+// loop over strided modes, one row per thread, that served orders other than powers
+// of two, per token of a stack of banks replayed from a graph: B = 37, D = 1001, d =
+// 10, 8 banks 48.6 -> 37.0 us; B = 1, D = 4077, d = 60, 15 banks 180 -> 59 us; B =
+// 231, D = 704, d = 37, 6 banks 306 -> 175 us.)  The row sum is a butterfly over
+// those lanes (DPP within 16 lanes).  Each thread serves NB batch rows of the same (c,
+// modes): lambda and R are loaded once for the NB rows, and every thread has NB
+// independent state loads in flight before it computes.  NB = 8
 // where that still gives 2048 wavefronts (two per SIMD), else 4 where that
 // does, else 2: small states are latency-bound, and more wavefronts with
 // fewer rows each finish sooner (B = 16, D = 768, d = 16: 1.95 us per step
 // with NB = 2 against 2.51 us with NB = 8; B = 64, D = 2048: 6.0 us with
 // NB = 8 against 6.3 us with NB = 4).  A workgroup is one wavefront
-// (64 / LPR channels x NB batch rows) up to LPR = 16; with LPR >= 32 (d >=
-// 64, two channels or fewer per wavefront) it is four wavefronts, so that
+// (64 / LPR channels x NB batch rows) up to LPR = 16; with LPR >= 32 (two
+// channels or fewer per wavefront) it is four wavefronts, so that
 // a workgroup covers 8 channels (B = 256, D = 2048, d = 64: 71 us per step
 // against 76 us with one-wavefront workgroups).
 //
@@ -45,8 +49,8 @@
 // of every batch row of the state, and whole 128-byte lines of u_t and y_t
 // stay with one L2.
 //
-// Generic path (any other d): lanes take single modes j, j + LPR, ...
-// (LPR = next power of two >= d, <= 64) or pairs, one batch row per thread.
+// Generic path (larger d, or a grid past its limits): lanes take single modes j, j +
+// LPR, ... (LPR = next power of two >= d, <= 64) or pairs, one batch row per thread.
 #include "lh_internal.hpp"
 
 namespace lh {
@@ -54,7 +58,7 @@ namespace {
 
 constexpr int kBlock = 256;  // generic path
 
-// fast path: threads per workgroup for LPR lanes per row
+// lanes path: threads per workgroup for LPR lanes per row
 constexpr int pairs_block(int lpr) { return lpr >= 32 ? 256 : 64; }
 constexpr int kXcds = 8;
 constexpr int kMaxRowsPerThread = 8;
@@ -141,19 +145,49 @@ __device__ __forceinline__ float re_dot_pair(float4 r, float4 x)
     return fmaf(r.x, x.x, fmaf(-r.y, x.y, fmaf(r.z, x.z, -r.w * x.w)));
 }
 
-// Fast path: LPR = d / 2 lanes per row, NB rows per thread, 2-D grid of
-// (channel tile, batch group) workgroups.  gridDim.x is the tile count padded
-// to a multiple of 8; workgroup x runs on XCD x % 8, which owns tiles
-// [(x % 8) T8, (x % 8 + 1) T8) with T8 = gridDim.x / 8.  NTL: non-temporal
-// state loads.
-template <typename IO, int LPR, bool NTL, int NB>
-__global__ __launch_bounds__(pairs_block(LPR)) void step_pairs_kernel(
+// The modes that a lane holds: two (16 bytes) or one (8 bytes, as a float4 whose
+// second half is zero and drops out of the compiled code).
+template <int VEC, bool NT>
+__device__ __forceinline__ float4 load_modes(const float2* p)
+{
+    if constexpr (VEC == 2) {
+        return load4<NT>(p);
+    } else {
+        typedef float f2v __attribute__((ext_vector_type(2)));
+        const f2v* q = reinterpret_cast<const f2v*>(p);
+        f2v v;
+        if constexpr (NT)
+            v = __builtin_nontemporal_load(q);
+        else
+            v = *q;
+        return make_float4(v.x, v.y, 0.f, 0.f);
+    }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_modes(float2* p, float4 a)
+{
+    if constexpr (VEC == 2) {
+        store4<true>(p, a);
+    } else {
+        typedef float f2v __attribute__((ext_vector_type(2)));
+        __builtin_nontemporal_store(f2v{a.x, a.y}, reinterpret_cast<f2v*>(p));
+    }
+}
+
+// Lanes path: LPR lanes per row of VEC modes each, NB rows per thread, 2-D grid of
+// (channel tile, batch group) workgroups.  FULL: d == VEC LPR; else lanes past d
+// hold zeros and touch no memory.  gridDim.x is the tile count padded to a multiple
+// of 8; workgroup x runs on XCD x % 8, which owns tiles [(x % 8) T8, (x % 8 + 1) T8)
+// with T8 = gridDim.x / 8.  NTL: non-temporal state loads.
+template <typename IO, int LPR, int VEC, bool FULL, bool NTL, int NB>
+__global__ __launch_bounds__(pairs_block(LPR)) void step_lanes_kernel(
     const float2* __restrict__ lam, const float2* __restrict__ R, const float* __restrict__ h0,
-    float2* __restrict__ state, const IO* __restrict__ u, IO* __restrict__ y, int B, int D,
+    float2* __restrict__ state, const IO* __restrict__ u, IO* __restrict__ y, int B, int D, int dr,
     int ntiles)
 {
     constexpr int kRows = pairs_block(LPR) / LPR;  // channels per workgroup
-    constexpr int d = 2 * LPR;
+    const int d = FULL ? VEC * LPR : dr;
     const int ct = int(blockIdx.x % kXcds) * int(gridDim.x / kXcds) + int(blockIdx.x / kXcds);
     const int b0 = blockIdx.y * NB;
     if (ct >= ntiles) return;  // padding tiles
@@ -161,16 +195,19 @@ __global__ __launch_bounds__(pairs_block(LPR)) void step_pairs_kernel(
     const int c = ct * kRows + threadIdx.x / LPR;
     const bool cvalid = c < D;
     const int cc = cvalid ? c : D - 1;  // every address stays in bounds
+    const bool on = FULL || VEC * j < d;  // d is a multiple of VEC
 
-    const float4 l4 = load4<false>(lam + int64_t(cc) * d + 2 * j);
-    const float4 r4 = load4<false>(R + int64_t(cc) * d + 2 * j);
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int64_t at = int64_t(cc) * d + VEC * j;
+    const float4 l4 = on ? load_modes<VEC, false>(lam + at) : zero;
+    const float4 r4 = on ? load_modes<VEC, false>(R + at) : zero;
     float4 x[NB];
     float uv[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int b = (b0 + i < B) ? b0 + i : B - 1;
         const int64_t row = int64_t(b) * D + cc;
-        x[i] = load4<NTL>(state + row * d + 2 * j);
+        x[i] = on ? load_modes<VEC, NTL>(state + row * d + VEC * j) : zero;
         uv[i] = io_load(u + row);
     }
     const float hz = h0[cc];
@@ -186,7 +223,7 @@ __global__ __launch_bounds__(pairs_block(LPR)) void step_pairs_kernel(
         const float4 n4 = step_pair(l4, x[i], uv[i]);
         if (cvalid && b < B) {
             const int64_t row = int64_t(b) * D + c;
-            store4<true>(state + row * d + 2 * j, n4);
+            if (on) store_modes<VEC>(state + row * d + VEC * j, n4);
             if (j == 0) io_store(y + row, fmaf(hz, uv[i], acc));
         }
     }
@@ -241,7 +278,7 @@ __global__ __launch_bounds__(kBlock) void step_generic_kernel(
     if (valid && j == 0) io_store(y + b * D + c, fmaf(h0[c], uv, acc));
 }
 
-// Batch rows per thread of the fast path (see the file comment).
+// Batch rows per thread of the lanes path (see the file comment).
 int pairs_rows_per_thread(int lpr, int64_t B, int64_t D)
 {
     const int64_t waves_per_group = (D * lpr + 63) / 64;
@@ -250,7 +287,7 @@ int pairs_rows_per_thread(int lpr, int64_t B, int64_t D)
     return 2;
 }
 
-// 2-D grid of the fast path; false when it does not fit the grid limits
+// 2-D grid of the lanes path; false when it does not fit the grid limits
 bool pairs_grid(int lpr, int nb, int64_t B, int64_t D, dim3* g, int* ntiles)
 {
     const int64_t rows_per_block = pairs_block(lpr) / lpr;
@@ -263,48 +300,70 @@ bool pairs_grid(int lpr, int nb, int64_t B, int64_t D, dim3* g, int* ntiles)
     return true;
 }
 
-template <typename IO, bool NTL, int NB>
-hipError_t launch_pairs(int lpr, dim3 grid, int ntiles, const float2* lam, const float2* R,
-                        const float* h0, float2* state, const void* u, void* y, int64_t B,
-                        int64_t D, hipStream_t stream)
+// One call's sizes and pointers, for the nest of template choices below.
+struct Step {
+    const float2 *lam, *R;
+    const float* h0;
+    float2* state;
+    const void* u;
+    void* y;
+    int B, D, d;
+    dim3 grid;
+    int ntiles;
+    hipStream_t stream;
+};
+
+template <typename IO, int LPR, int VEC, bool FULL, bool NTL>
+hipError_t launch_nb(int nb, const Step& s)
 {
-    const IO* uu = static_cast<const IO*>(u);
-    IO* yy = static_cast<IO*>(y);
-    const int b = int(B), dd = int(D);
-#define LH_PAIRS(L)                                                                          \
-    case L:                                                                                  \
-        hipLaunchKernelGGL((step_pairs_kernel<IO, L, NTL, NB>), grid, dim3(pairs_block(L)), 0, \
-                           stream, lam, R, h0, state, uu, yy, b, dd, ntiles);                \
-        break;
-    switch (lpr) {
-        LH_PAIRS(1)
-        LH_PAIRS(2)
-        LH_PAIRS(4)
-        LH_PAIRS(8)
-        LH_PAIRS(16)
-        LH_PAIRS(32)
-        LH_PAIRS(64)
-        default:
-            return hipErrorInvalidValue;
+#define LH_NB(N)                                                                             \
+    case N:                                                                                  \
+        hipLaunchKernelGGL((step_lanes_kernel<IO, LPR, VEC, FULL, NTL, N>), s.grid,          \
+                           dim3(pairs_block(LPR)), 0, s.stream, s.lam, s.R, s.h0, s.state,   \
+                           static_cast<const IO*>(s.u), static_cast<IO*>(s.y), s.B, s.D, s.d, \
+                           s.ntiles);                                                        \
+        return hipGetLastError();
+    switch (nb) {
+        LH_NB(8)
+        LH_NB(4)
+        LH_NB(2)
+        default: return hipErrorInvalidValue;
     }
-#undef LH_PAIRS
-    return hipGetLastError();
+#undef LH_NB
 }
 
-template <typename IO, bool NTL>
-hipError_t launch_pairs_nb(int nb, int lpr, dim3 grid, int ntiles, const float2* lam,
-                           const float2* R, const float* h0, float2* state, const void* u, void* y,
-                           int64_t B, int64_t D, hipStream_t stream)
+template <typename IO, int LPR, int VEC, bool FULL>
+hipError_t launch_ntl(bool ntl, int nb, const Step& s)
 {
-    switch (nb) {
-        case 8:
-            return launch_pairs<IO, NTL, 8>(lpr, grid, ntiles, lam, R, h0, state, u, y, B, D, stream);
-        case 4:
-            return launch_pairs<IO, NTL, 4>(lpr, grid, ntiles, lam, R, h0, state, u, y, B, D, stream);
-        case 2:
-            return launch_pairs<IO, NTL, 2>(lpr, grid, ntiles, lam, R, h0, state, u, y, B, D, stream);
-        default:
-            return hipErrorInvalidValue;
+    return ntl ? launch_nb<IO, LPR, VEC, FULL, true>(nb, s)
+               : launch_nb<IO, LPR, VEC, FULL, false>(nb, s);
+}
+
+template <typename IO, int LPR>
+hipError_t launch_vec(int vec, bool ntl, int nb, const Step& s)
+{
+    const bool full = s.d == vec * LPR;
+    if (vec == 2) {
+        if (full) return launch_ntl<IO, LPR, 2, true>(ntl, nb, s);
+        if constexpr (LPR >= 4) return launch_ntl<IO, LPR, 2, false>(ntl, nb, s);
+        return hipErrorInvalidValue;  // 2 LPR - d < LPR: none below 4
+    }
+    // single modes have no fully unrolled form: odd d never fills LPR > 1
+    return launch_ntl<IO, LPR, 1, false>(ntl, nb, s);
+}
+
+template <typename IO>
+hipError_t launch_lanes(int lpr, int vec, bool ntl, int nb, const Step& s)
+{
+    switch (lpr) {
+        case 1: return launch_vec<IO, 1>(vec, ntl, nb, s);
+        case 2: return launch_vec<IO, 2>(vec, ntl, nb, s);
+        case 4: return launch_vec<IO, 4>(vec, ntl, nb, s);
+        case 8: return launch_vec<IO, 8>(vec, ntl, nb, s);
+        case 16: return launch_vec<IO, 16>(vec, ntl, nb, s);
+        case 32: return launch_vec<IO, 32>(vec, ntl, nb, s);
+        case 64: return launch_vec<IO, 64>(vec, ntl, nb, s);
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -347,23 +406,17 @@ hipError_t launch_step(const float2* lam, const float2* R, const float* h0, floa
 {
     (void)hipGetLastError();  // clear a stale error so the status below is this launch's
     const int64_t pairs = d / 2;
-    const bool pow2_pairs = d % 2 == 0 && pairs >= 1 && pairs <= 64 && (pairs & (pairs - 1)) == 0;
-    dim3 grid;
-    int ntiles = 0;
-    const int fast_lpr = static_cast<int>(pairs);
-    const int nb = pow2_pairs ? pairs_rows_per_thread(fast_lpr, B, D) : 2;
-    if (pow2_pairs && aligned16 && B < (INT64_C(1) << 31) && D < (INT64_C(1) << 31) &&
-        pairs_grid(fast_lpr, nb, B, D, &grid, &ntiles)) {
-        const bool ntl = 8 * B * D * d <= kStreamStateBytes;
-        if (bf16_io)
-            return ntl ? launch_pairs_nb<bf16, true>(nb, fast_lpr, grid, ntiles, lam, R, h0,
-                                                     state, u_t, y_t, B, D, stream)
-                       : launch_pairs_nb<bf16, false>(nb, fast_lpr, grid, ntiles, lam, R, h0,
-                                                      state, u_t, y_t, B, D, stream);
-        return ntl ? launch_pairs_nb<float, true>(nb, fast_lpr, grid, ntiles, lam, R, h0, state,
-                                                  u_t, y_t, B, D, stream)
-                   : launch_pairs_nb<float, false>(nb, fast_lpr, grid, ntiles, lam, R, h0, state,
-                                                   u_t, y_t, B, D, stream);
+    const int vec = d % 2 == 0 && aligned16 ? 2 : 1;
+    int fast_lpr = 1;
+    while (int64_t(fast_lpr) * vec < d) fast_lpr *= 2;
+    if (fast_lpr <= 64 && B < (INT64_C(1) << 31) && D < (INT64_C(1) << 31)) {
+        const int nb = pairs_rows_per_thread(fast_lpr, B, D);
+        Step s{lam, R, h0, state, u_t, y_t, int(B), int(D), int(d), dim3(), 0, stream};
+        if (pairs_grid(fast_lpr, nb, B, D, &s.grid, &s.ntiles)) {
+            const bool ntl = 8 * B * D * d <= kStreamStateBytes;
+            return bf16_io ? launch_lanes<bf16>(fast_lpr, vec, ntl, nb, s)
+                           : launch_lanes<float>(fast_lpr, vec, ntl, nb, s);
+        }
     }
     // generic layouts
     int lpr = 1;

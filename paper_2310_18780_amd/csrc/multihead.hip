@@ -14,11 +14,11 @@
 // once: bound by memory bandwidth like the per-channel step, with the head's
 // lambda and R shared by its N x N entries.
 //
-// Fast path (d even, d/2 a power of two <= 64, 16-byte aligned arrays): a
+// Lanes path (d even up to 128 in 16-byte aligned arrays, else d up to 64): a
 // wavefront owns one output row (b, m, i) and streams its N x d state, which
-// is contiguous; LPR = d/2 lanes hold the d modes of one entry (two modes and
-// one 16-byte access per lane), so a wave covers 64 / LPR entries per access
-// and one contiguous kilobyte.  The entry loop is unrolled four times so that
+// is contiguous; LPR lanes, the power of two that holds them, take the d modes of
+// one entry (two modes in 16 bytes or one in 8 per lane; lanes past d hold zeros),
+// so a wave covers 64 / LPR entries per access and a contiguous span.  The entry loop is unrolled four times so that
 // every lane has four state loads in flight.  Each lane accumulates q_j times
 // its share of w[i,j] over all its entries; one reduction over the wave gives
 // y.  A workgroup is four waves = four consecutive rows i of one (b, m), which
@@ -26,8 +26,9 @@
 // bench state: non-temporal state stores, 2 or 8 rows per workgroup and
 // unrolling by 2 or 8 were all within 2%, none faster.)
 //
-// Generic path (any other d or alignment): a wavefront per row as well, one
-// entry per lane and a loop over the modes.
+// Generic path (larger d): a wavefront per row as well, one entry per lane and a
+// loop over the modes (B = 8, M = 12, N = 103, d = 17 ran 270 us there, 90 us in the
+// lanes path).
 #include "lh_internal.hpp"
 
 namespace lh {
@@ -38,16 +39,24 @@ constexpr int kUnroll = 4;
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float4 ld4(const float2* p)
+template <int VEC>
+__device__ __forceinline__ float4 ld(const float2* p)
 {
-    const f4v v = *reinterpret_cast<const f4v*>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
+    if constexpr (VEC == 2) {
+        const f4v v = *reinterpret_cast<const f4v*>(p);
+        return make_float4(v.x, v.y, v.z, v.w);
+    } else {
+        return make_float4(p->x, p->y, 0.f, 0.f);
+    }
 }
 
-__device__ __forceinline__ void st4(float2* p, float4 a)
+template <int VEC>
+__device__ __forceinline__ void st(float2* p, float4 a)
 {
-    const f4v v = {a.x, a.y, a.z, a.w};
-    *reinterpret_cast<f4v*>(p) = v;
+    if constexpr (VEC == 2)
+        *reinterpret_cast<f4v*>(p) = f4v{a.x, a.y, a.z, a.w};
+    else
+        *p = make_float2(a.x, a.y);
 }
 
 // sum over the 64 lanes of a wave, returned in every lane: DPP within rows of
@@ -72,13 +81,16 @@ __device__ __forceinline__ float wave_sum(float v)
     return (r0 + r1) + (r2 + r3);
 }
 
-template <typename IO, int LPR>
-__global__ __launch_bounds__(64 * kWaves) void mh_step_pairs_kernel(
+// VEC modes per lane (two in 16 bytes, or one in 8: then the second half of every
+// float4 is zero and drops out of the compiled code); FULL: d == VEC LPR, else lanes
+// past d hold zeros and touch no memory
+template <typename IO, int LPR, int VEC, bool FULL>
+__global__ __launch_bounds__(64 * kWaves) void mh_step_lanes_kernel(
     const float2* __restrict__ lam, const float2* __restrict__ R, const float* __restrict__ h0,
     float2* __restrict__ state, const IO* __restrict__ q, const IO* __restrict__ k,
-    const IO* __restrict__ v, IO* __restrict__ y, int M, int N, int64_t nrowblk)
+    const IO* __restrict__ v, IO* __restrict__ y, int M, int N, int dr, int64_t nrowblk)
 {
-    constexpr int d = 2 * LPR;
+    const int d = FULL ? VEC * LPR : dr;
     constexpr int G = 64 / LPR;  // entries per access of the wave
     const int64_t blk = blockIdx.x;
     if (blk >= nrowblk) return;
@@ -88,11 +100,13 @@ __global__ __launch_bounds__(64 * kWaves) void mh_step_pairs_kernel(
     if (i >= N) return;  // whole wave
     const int m = int(bm % M);
     const int lane = threadIdx.x % 64;
-    const int p = lane % LPR;   // mode pair of this lane
+    const int p = lane % LPR;   // which of the row's lanes
+    const bool on = FULL || VEC * p < d;  // d is a multiple of VEC
     const int e = lane / LPR;   // entry offset within an access
 
-    const float4 l4 = ld4(lam + int64_t(m) * d + 2 * p);
-    const float4 r4 = ld4(R + int64_t(m) * d + 2 * p);
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 l4 = on ? ld<VEC>(lam + int64_t(m) * d + VEC * p) : zero;
+    const float4 r4 = on ? ld<VEC>(R + int64_t(m) * d + VEC * p) : zero;
     const float hz = p == 0 ? h0[m] : 0.f;  // the pass-through term once per entry
     const int64_t io0 = bm * N;               // first channel of head m in row b
     const float ki = io_load(k + io0 + i);
@@ -105,7 +119,7 @@ __global__ __launch_bounds__(64 * kWaves) void mh_step_pairs_kernel(
 #pragma unroll
         for (int s = 0; s < kUnroll; ++s) {
             const int j = min(j0 + s * G + e, N - 1);  // clamped: every address in range
-            x[s] = ld4(xrow + int64_t(j) * d + 2 * p);
+            x[s] = on ? ld<VEC>(xrow + int64_t(j) * d + VEC * p) : zero;
             vj[s] = io_load(v + io0 + j);
             qj[s] = io_load(q + io0 + j);
         }
@@ -122,7 +136,7 @@ __global__ __launch_bounds__(64 * kWaves) void mh_step_pairs_kernel(
             n4.w = fmaf(l4.z, x[s].w, l4.w * x[s].z);
             if (j < N) {
                 acc = fmaf(qj[s], w, acc);
-                st4(xrow + int64_t(j) * d + 2 * p, n4);
+                if (on) st<VEC>(xrow + int64_t(j) * d + VEC * p, n4);
             }
         }
     }
@@ -181,26 +195,32 @@ hipError_t launch(const float2* lam, const float2* R, const float* h0, float2* s
     IO* yy = static_cast<IO*>(y);
     const dim3 grid(static_cast<uint32_t>(nrowblk));
     const dim3 block(64 * kWaves);
-    const int64_t pairs = d / 2;
-    const bool pow2 = d % 2 == 0 && pairs >= 1 && pairs <= 64 && (pairs & (pairs - 1)) == 0;
-    if (pow2 && aligned16) {
-        switch (pairs) {
+    const int vec = d % 2 == 0 && aligned16 ? 2 : 1;
+    int lpr = 1;
+    while (int64_t(lpr) * vec < d) lpr *= 2;
+    switch (lpr) {
+#define LH_MH_LAUNCH(L, V, F)                                                                 \
+    hipLaunchKernelGGL((mh_step_lanes_kernel<IO, L, V, F>), grid, block, 0, stream, lam, R,   \
+                       h0, state, qq, kk, vv, yy, int(M), int(N), int(d), nrowblk)
 #define LH_MH(L)                                                                              \
     case L:                                                                                   \
-        hipLaunchKernelGGL((mh_step_pairs_kernel<IO, L>), grid, block, 0, stream, lam, R, h0, \
-                           state, qq, kk, vv, yy, int(M), int(N), nrowblk);                  \
+        if (vec == 1)                                                                         \
+            LH_MH_LAUNCH(L, 1, false);                                                        \
+        else if (d == 2 * L)                                                                  \
+            LH_MH_LAUNCH(L, 2, true);                                                         \
+        else                                                                                  \
+            LH_MH_LAUNCH(L, 2, false);                                                        \
         return hipGetLastError();
-            LH_MH(1)
-            LH_MH(2)
-            LH_MH(4)
-            LH_MH(8)
-            LH_MH(16)
-            LH_MH(32)
-            LH_MH(64)
+        LH_MH(1)
+        LH_MH(2)
+        LH_MH(4)
+        LH_MH(8)
+        LH_MH(16)
+        LH_MH(32)
+        LH_MH(64)
 #undef LH_MH
-            default:
-                break;
-        }
+#undef LH_MH_LAUNCH
+        default: break;  // more modes than a wavefront's lanes hold
     }
     hipLaunchKernelGGL((mh_step_generic_kernel<IO>), grid, block, 0, stream, lam, R, h0, state,
                        qq, kk, vv, yy, int(M), int(N), int(d), nrowblk);
