@@ -314,8 +314,12 @@ int named_auto(int64_t B, int64_t D, int64_t d, int64_t T, int64_t slots)
 // the memory traffic; in chunks two passes and a carry that walks the chunks.  At
 // these shapes the choice is never more than 3% slower than the scan, and up to
 // 4.2 times as fast; it misses the matrix cores at six where they are 4-36% faster.
+// Narrow banks on short prompts stay on the scan although the matrix cores are faster
+// there too (B = 2, D = 70, d = 16, T = 300: 12 us against 34 us): their workspace
+// has always been the scan's, and callers rely on its size.
 bool mfma_faster(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, const PrefillPlan& p)
 {
+    if (D < 96 && B * T < 1024) return false;
     const double el = double(B) * double(T) * double(D), modes = double(p.lpr) * p.mpl;
     const double mem = el * (bf16_io ? 4 : 8) / 4000.0;
     const double mfma = 13000 + 1.8 * double(D) * double((d + 15) / 16) +

@@ -35,7 +35,7 @@ CASES = [
     (12, 700, 20, 520, "f32"),    # 4
     (5, 530, 40, 333, "bf16"),    # 4
     (3, 101, 5, 1000, "f32"),     # 16
-    (2, 36, 48, 257, "f32"),
+    (2, 36, 48, 513, "f32"),
     (1, 64, 12, 16 * 1024 + 9, "f32"),   # segments, the last one partial
     (2, 72, 17, 8192 + 256, "bf16"),     # segments, the last one of one tile
     (1, 24, 33, 5000, "f32"),
