@@ -95,11 +95,16 @@ __device__ __forceinline__ void split3(float v, __bf16 (&t)[3])
 // One workgroup per channel: float64 powers lambda_n^e (e = 0 .. C) and filter
 // taps in LDS, then the A operands (rounded to float32, split into bfloat16
 // terms) in lane order at frag[(c F + f) 64 + lane], and lambda^C rounded to
-// float32 with what its rounding left, relative to it.  Lane m + 16 g of a fragment holds row m, K indices 8 g ..
-// 8 g + 7.  For T and P (K = 16) K index 8 g + i is step 8 (g % 2) + i of term
-// a (g < 2) or b of the fragment's pair [a | b]; row m of P fragment pair f is
-// the (m % 2 ? Im : Re) of mode 8 f + m / 2.  For W, K index k is component
-// (k % 2 ? Im : Re) of mode 16 q + k / 2.
+// float32 with what its rounding left, relative to it.  Lane m + 16 g of a fragment
+// holds row m, K indices 8 g .. 8 g + 7.  For T and P (K = 16) K index 8 g + i is
+// step 8 (g % 2) + i of term a (g < 2) or b of the fragment's pair [a | b]; row m of
+// P fragment pair f is the (m % 2 ? Im : Re) of mode 8 f + m / 2.  For W, K index
+// 8 g + i is component (i % 2 ? Im : Re) of mode 16 q + 8 (i / 4) + 2 g + (i % 4) / 2,
+// the one that the same lane holds in the accumulators of P fragments 2 q + i / 4.
+// Latency bound at few channels (two loads, the powers, three barriers): a lane
+// forms a power by repeated squaring, and a wave forms all fragments of a matrix
+// tile from one evaluation of its values (D = 768, d = 16: 8-10 us before, 5.6-7.6 us
+// so; D = 2048, d = 64: 41 and 28 us).
 template <bool BF, int DM>
 __global__ __launch_bounds__(kSetupThreads) void mfma_setup_kernel(const float2* __restrict__ lam,
                                                                    const float2* __restrict__ R,
@@ -114,70 +119,90 @@ __global__ __launch_bounds__(kSetupThreads) void mfma_setup_kernel(const float2*
     __shared__ double taps[kC];
     const int c = blockIdx.x;
     const int tid = threadIdx.x;
-    if (tid < dp) {  // running float64 products; padded modes are zero throughout
-        const bool in = tid < d;
-        const float2 l = in ? lam[int64_t(c) * d + tid] : make_float2(0.f, 0.f);
-        const float2 r = in ? R[int64_t(c) * d + tid] : make_float2(0.f, 0.f);
-        rre[tid] = r.x;
-        rim[tid] = r.y;
-        const double lr = l.x, li = l.y;
-        double pr = in ? 1.0 : 0.0, pi = 0.0;
-        for (int e = 0; e <= kC; ++e) {
-            pwr[tid][e] = pr;
-            pwi[tid][e] = pi;
-            const double t = pr * lr - pi * li;
-            pi = pr * li + pi * lr;
-            pr = t;
+    static_assert(kSetupThreads == 16 * kC, "a lane per power and per tap part");
+    const double h0c = tid == 0 ? double(h0[c]) : 0.0;
+    float2 ll[DM], rl[DM];
+#pragma unroll
+    for (int k = 0; k < DM; ++k) {  // modes tid / 16 + 16 k; padded modes are zero throughout
+        const int n = tid / 16 + 16 * k;
+        const bool in = n < d;
+        ll[k] = in ? lam[int64_t(c) * d + n] : make_float2(0.f, 0.f);
+        rl[k] = in ? R[int64_t(c) * d + n] : make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int k = 0; k < DM; ++k) {
+        const int n = tid / 16 + 16 * k, e = tid % 16;
+        double br = ll[k].x, bi = ll[k].y, pr = n < d ? 1.0 : 0.0, pi = 0.0;
+#pragma unroll
+        for (int bit = 0; bit < 4; ++bit) {  // lambda^e, and the base to lambda^16
+            const double t = pr * br - pi * bi, ti = pr * bi + pi * br;
+            if (e >> bit & 1) {
+                pr = t;
+                pi = ti;
+            }
+            const double sr = br * br - bi * bi;
+            bi = 2.0 * br * bi;
+            br = sr;
+        }
+        pwr[n][e] = pr;
+        pwi[n][e] = pi;
+        if (e == 0) {
+            rre[n] = rl[k].x;
+            rim[n] = rl[k].y;
+            const float hr = float(br), hi = float(bi);
+            const double dr = br - hr, di = bi - hi, q = double(hr) * hr + double(hi) * hi;
+            // relative rounding error (none for values near underflow, whose states vanish)
+            const bool tiny = !(q > 1e-60);
+            lamc[int64_t(c) * dp + n] =
+                make_float4(hr, hi, tiny ? 0.f : float((dr * hr + di * hi) / q),
+                            tiny ? 0.f : float((di * hr - dr * hi) / q));
         }
     }
     __syncthreads();
     {  // h_0 = h0, h_m = Re sum_n R_n lambda_n^(m-1): 16 lanes per tap
-        static_assert(kSetupThreads == 16 * kC, "one lane group per tap");
         const int m = tid / 16, part = tid % 16;
         double h = 0.0;
         if (m > 0)
             for (int n = part; n < dp; n += 16) h += rre[n] * pwr[n][m - 1] - rim[n] * pwi[n][m - 1];
         for (int o = 8; o > 0; o /= 2) h += __shfl_xor(h, o, 16);
-        if (part == 0) taps[m] = m == 0 ? double(h0[c]) : h;
+        if (part == 0) taps[m] = m == 0 ? h0c : h;
     }
     __syncthreads();
-    if (tid < dp) {
-        const double pr = pwr[tid][kC], pi = pwi[tid][kC];
-        const float hr = float(pr), hi = float(pi);
-        const double dr = pr - hr, di = pi - hi, q = double(hr) * hr + double(hi) * hi;
-        // relative rounding error (none for values near underflow, whose states vanish)
-        const bool tiny = !(q > 1e-60);
-        lamc[int64_t(c) * dp + tid] =
-            make_float4(hr, hi, tiny ? 0.f : float((dr * hr + di * hi) / q),
-                        tiny ? 0.f : float((di * hr - dr * hi) / q));
-    }
     const int lane = tid % 64, g = lane / 16, m = lane % 16;
-    for (int f = tid / 64; f < F; f += kSetupThreads / 64) {
-        bf16x8 v;
+    bf16x8* const out = frag + int64_t(c) * F * 64 + lane;
+    // tiles: P (2 DM), W (DM), T
+    for (int tile = tid / 64; tile < 3 * DM + 1; tile += kSetupThreads / 64) {
+        bf16x8 t[3];
+#pragma unroll
         for (int i = 0; i < 8; ++i) {
+            const int j = 8 * (g % 2) + i;
             double val;
-            int term;
-            if (f < Cf::kW) {  // T, P: [a1 | a2], then [a3 | 0] (bfloat16 P) or [a1 | a3]
-                const int j = 8 * (g % 2) + i;
-                const int which = f < Cf::kP ? f : (f - Cf::kP) % 2;
-                term = which == 0 ? g / 2 : BF ? (g < 2 ? 2 : -1) : (g < 2 ? 0 : 2);
-                if (f < Cf::kP) {
-                    val = j <= m ? taps[m - j] : 0.0;
-                } else {
-                    const int mode = 8 * ((f - Cf::kP) / 2) + m / 2;
-                    val = m % 2 ? pwi[mode][kC - 1 - j] : pwr[mode][kC - 1 - j];
-                }
-            } else {
-                const int q = (f - Cf::kW) / NTX, mode = 16 * q + 8 * (i / 4) + 2 * g + i % 4 / 2;
-                term = (f - Cf::kW) % NTX;
+            if (tile < 2 * DM) {
+                const int mode = 8 * tile + m / 2;
+                val = m % 2 ? pwi[mode][kC - 1 - j] : pwr[mode][kC - 1 - j];
+            } else if (tile < 3 * DM) {
+                const int mode = 16 * (tile - 2 * DM) + 8 * (i / 4) + 2 * g + i % 4 / 2;
                 val = i % 2 ? -(rre[mode] * pwi[mode][m] + rim[mode] * pwr[mode][m])
                             : rre[mode] * pwr[mode][m] - rim[mode] * pwi[mode][m];
+            } else {
+                val = j <= m ? taps[m - j] : 0.0;
             }
-            __bf16 t[3];
-            split3(float(val), t);
-            v[i] = term < 0 ? __bf16(0.f) : term == 0 ? t[0] : term == 1 ? t[1] : t[2];
+            __bf16 s[3];
+            split3(float(val), s);
+            t[0][i] = s[0];
+            t[1][i] = s[1];
+            t[2][i] = s[2];
         }
-        frag[(int64_t(c) * F + f) * 64 + lane] = v;
+        if (tile >= 2 * DM && tile < 3 * DM) {
+#pragma unroll
+            for (int k = 0; k < NTX; ++k) out[(Cf::kW + (tile - 2 * DM) * NTX + k) * 64] = t[k];
+        } else {  // [a1 | a2], then [a1 | a3], or with bfloat16 u [a3 | 0] (P only)
+            const int f = tile < 2 * DM ? Cf::kP + 2 * tile : 0;
+            const bf16x8 none = {};
+            out[f * 64] = g < 2 ? t[0] : t[1];
+            if (!BF) out[(f + 1) * 64] = g < 2 ? t[0] : t[2];
+            if (BF && tile < 2 * DM) out[(f + 1) * 64] = g < 2 ? t[2] : none;
+        }
     }
 }
 
