@@ -453,16 +453,21 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
 #pragma unroll
             for (int k = 0; k < CPW; ++k) {
                 const float2* l1 = p.lam + int64_t(min(c0 + w * CPW + k, D - 1)) * d;
-                for (int j = 0; j < tr; ++j) {
-                    const float uv = u_at(ub, k, n, j);
+                f32x4 l[2 * DM];  // all loads before the chain of steps
 #pragma unroll
-                    for (int f = 0; f < 2 * DM; ++f) {
-                        const int m0 = 8 * f + 2 * g;
-                        const float2 a = m0 < d ? l1[m0] : make_float2(0.f, 0.f);
-                        const float2 b = m0 + 1 < d ? l1[m0 + 1] : make_float2(0.f, 0.f);
-                        X[k][f] = mul_lambda(f32x4{a.x, a.y, b.x, b.y}, X[k][f]) +
-                                  f32x4{uv, 0.f, uv, 0.f};
-                    }
+                for (int f = 0; f < 2 * DM; ++f) {
+                    const int m0 = 8 * f + 2 * g;
+                    const float2 a = m0 < d ? l1[m0] : make_float2(0.f, 0.f);
+                    const float2 b = m0 + 1 < d ? l1[m0 + 1] : make_float2(0.f, 0.f);
+                    l[f] = f32x4{a.x, a.y, b.x, b.y};
+                }
+                float uv = u_at(ub, k, n, 0);
+                for (int j = 0; j < tr; ++j) {
+                    const float un = u_at(ub, k, n, min(j + 1, kC - 1));
+#pragma unroll
+                    for (int f = 0; f < 2 * DM; ++f)
+                        X[k][f] = mul_lambda(l[f], X[k][f]) + f32x4{uv, 0.f, uv, 0.f};
+                    uv = un;
                 }
             }
         }
@@ -515,18 +520,24 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
             } else {  // whole chunks, then the remaining steps one by one
                 const float2 l1 = sm < d ? p.lam[int64_t(sc) * d + sm] : make_float2(0.f, 0.f);
                 const int left = int(nfull - int64_t(tile) * S);
+                for (int s = 0; s < left; ++s)
 #pragma unroll
-                for (int r = 0; r < RL; ++r) {
-                    float2* e = xp + r * S * (XST / 2);
-                    for (int s = 0; s < left; ++s, e += XST / 2) {
+                    for (int r = 0; r < RL; ++r) {
+                        float2* e = xp + (r * S + s) * (XST / 2);
                         const float2 z = *e;
                         *e = make_float2(xr[r], xi[r]);
                         advance(r, z);
                     }
-                    *e = make_float2(xr[r], xi[r]);
-                    for (int j = 0; j < tr; ++j) {
-                        const float uv = u_at(ub, sk, (srh * RL + r) * S + left, j);
-                        const float nr = fmaf(l1.x, xr[r], fmaf(-l1.y, xi[r], uv));
+#pragma unroll
+                for (int r = 0; r < RL; ++r)
+                    xp[(r * S + left) * (XST / 2)] = make_float2(xr[r], xi[r]);
+                for (int j = 0; j < tr; ++j) {  // the rows of a lane side by side
+                    float uv[RL];
+#pragma unroll
+                    for (int r = 0; r < RL; ++r) uv[r] = u_at(ub, sk, (srh * RL + r) * S + left, j);
+#pragma unroll
+                    for (int r = 0; r < RL; ++r) {
+                        const float nr = fmaf(l1.x, xr[r], fmaf(-l1.y, xi[r], uv[r]));
                         xi[r] = fmaf(l1.x, xi[r], l1.y * xr[r]);
                         xr[r] = nr;
                     }
