@@ -293,16 +293,29 @@ namespace {
 
 constexpr int64_t kMaxSegments = 64;
 
-// The named plan of an automatic call at sizes that the explicit requests take:
-// the whole prompt where its (channel, row) tiles fill the GPU or there are 16
-// rows and more, the segmented plan for fewer rows of a prompt that splits; at
-// d = 64 also the whole prompt from 4 rows on.
-int named_auto(int64_t B, int64_t D, int64_t d, int64_t T, int64_t slots)
+// The named plan of an automatic call at sizes that the explicit requests take.  It
+// fixes the workspace, which callers hold, so the rule stays as it is whatever the
+// kernel's tiling: the whole prompt where its (16 channels, 32 rows) tiles fill the
+// GPU, or where it walks at most 7/5 of the chunks of 32 steps that the busiest CU
+// walks in the two passes of the segmented plan, counted in workgroups of `cw`
+// channels and 16 or 32 rows.
+int named_auto(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64_t slots)
 {
     if (d == 64 && B < 4 && B * T <= 1024) return 0;
     if ((D + 15) / 16 * ((B + 31) / 32) >= 256) return 1;
-    if (slots >= 2) return B >= 16 ? 1 : 2;
-    return d == 64 && B >= 4 ? 1 : 0;
+    if (slots >= 2) {
+        auto walk = [&](int64_t rows, int64_t chunks, bool states_only) {
+            const int64_t cw = d == 64 ? 4 : (d == 16 && bf16_io ? 16 : 8) * (states_only ? 2 : 1);
+            const int64_t groups = d == 16 && !bf16_io && rows > 16 ? 2 : 1;
+            const int64_t wgs = (D + cw - 1) / cw * ((rows + 16 * groups - 1) / (16 * groups));
+            return (wgs + 255) / 256 * chunks * groups;
+        };
+        const int64_t chunks = T / slots / 32;
+        const int64_t segmented =
+            walk(B * (slots - 1), chunks, true) + walk(B * slots, chunks, false);
+        return 5 * walk(B, (T + 31) / 32, false) <= 7 * segmented ? 1 : 2;
+    }
+    return d == 64 && (B >= 4 || (D + 3) / 4 * ((B + 15) / 16) >= 256) ? 1 : 0;
 }
 
 // Whether sizes that no explicit request names run faster on the matrix cores
@@ -403,14 +416,25 @@ bool make_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t reque
     const int64_t slots = supported ? mfma_segments(B, D, d, T) : 0;
     if (p.forced && (!supported || (request == -2 && slots < 2))) return false;
     p.named = p.forced ? -static_cast<int>(request)
-              : request == 0 && supported ? named_auto(B, D, d, T, slots)
+              : request == 0 && supported ? named_auto(B, D, d, T, bf, slots)
                                           : 0;
     const bool possible = mfma_possible(B, D, d, T, bf);
     if (p.named == 1) {
         p.mfma = possible;
-        p.cut = mfma_cut(B, D, d, T, bf, 1);
         const size_t mb = mfma_workspace_bytes(D, d);
         if (p.forced || mb > p.ws_bytes) p.ws_bytes = mb;
+        // an automatic call is cut into segments too where its workspace, sized
+        // for the scan, has room for their states
+        p.cut = mfma_cut(B, D, d, T, bf, p.forced ? 1 : slots);
+        if (p.cut.nseg > 1) {
+            const size_t off =
+                (p.off_xin + static_cast<size_t>(B) * p.cut.nseg * D * d * sizeof(float2) + 255) /
+                256 * 256;
+            if (off + mfma_table_bytes(bf, D, d) <= p.ws_bytes)
+                p.off_mfma = off;
+            else
+                p.cut = mfma_cut(B, D, d, T, bf, 1);
+        }
     } else if (p.named == 2) {
         p.mfma = possible;
         p.cut = mfma_cut(B, D, d, T, bf, slots);
