@@ -146,14 +146,12 @@ def prefill_flops(w):
 
 def mfma64_flops(w):
     """Flops the d = 64 matrix-core plan executes (16x16x32 bfloat16
-    products, 16384 flops each; float32 operands in three bfloat16 terms, six
-    term products per contraction): per channel, 16-row column block and
-    32-step chunk, 48 products for the chunk's end state (8 row tiles of P U),
-    12 for the outputs from the chunk's inputs (2 row tiles of T U) and 32 for
-    those from its entry state (W X: 2 row tiles x 4 K tiles x 4 term
-    products); a partial last chunk takes the 44 output products only."""
-    full, part = w.T // 32, int(w.T % 32 != 0)
-    return 16384 * w.D * -(-w.B // 16) * (92 * full + 44 * part)
+    products, 16384 flops each; float32 operands in three bfloat16 terms): per
+    channel, 16 columns (rows, or chunks of a row) of a 16-step chunk, 24
+    products for the chunk's end state (8 row tiles of P U, K holding two terms
+    of 16 steps), 3 for the outputs from the chunk's inputs (T U) and 16 for
+    those from its entry state (W X: 4 K tiles x 4 term products)."""
+    return 16384 * w.D * -(-w.B // 16) * 43 * -(-w.T // 16)
 
 
 def dtype_detail(w, plan):
@@ -429,7 +427,7 @@ def distill_main(args):
         "ms_per_call": ms,
         "roofline": {"bound": "alu", "achieved": tf, "peak": FP32_VALU_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": tf / FP32_VALU_PEAK_TFLOPS, "traffic": None,
-                     "kernel": "distill_kernel", "flops_per_launch": flops,
+                     "kernel": "distill_mfma_kernel" if w.d <= 64 else "distill_kernel", "flops_per_launch": flops,
                      "bytes_per_launch": nbytes, "gbps": nbytes / (ms * 1e-3) / 1e9},
         "cpu_baseline": cpu,
     }
@@ -890,15 +888,16 @@ def main():
     pre_tf = prefill_flops(w) / (pre_avg * 1e-3) / 1e12
     traffic = counter_traffic(f"decode_step_{w.name}_counters.txt",
                               src_digest("decode.hip", "lh_internal.hpp"))
-    pre_digest = src_digest("prefill.hip", "prefill_mfma.hip", "lh_internal.hpp")
+    pre_digest = src_digest("prefill.hip", "prefill_mfma.hip", "prefill_mfma.hpp",
+                            "prefill_mfma_kernel.hpp", "lh_internal.hpp")
     traffic_pre = counter_traffic(f"prefill_{w.name}_counters.txt", pre_digest)
     # The matrix-core plans at d = 16 and 32 execute their split-term
-    # contractions far below the bfloat16 MFMA ridge (at most 208 flops per
-    # byte of u and y against 2500 / 8 = 312), so their roofline is HBM; at
-    # d = 64 the 92 products per channel, 16 rows and 32 steps come to 368
-    # flops per byte, above the ridge, so its roofline is the bfloat16 MFMA
-    # peak; the VALU scan executes about the declared flops at high
-    # intensity, so its roofline is the VALU peak.
+    # contractions below the bfloat16 MFMA ridge (at most 240 flops per byte of
+    # u and y, d = 32 with bfloat16 u and y, against 2500 / 8 = 312), so their
+    # roofline is HBM; at d = 64 the 43 products per channel, 16 columns and 16
+    # steps come to 344 flops per byte, above the ridge, so its roofline is the
+    # bfloat16 MFMA peak; the general scan (plan "scan") is held against the VALU
+    # peak, which its declared flops reach on the VALU.
     plan = lh.prefill_plan(w.B, w.D, w.d, w.T, io=w.io)
     pre_gbs = prefill_bytes(w) / (pre_avg * 1e-3) / 1e9
     if plan == "scan":
@@ -963,7 +962,7 @@ def main():
                 "frac": dec_gbs / HBM_PEAK_GBS, "traffic": traffic,
                 "traffic_gbps": (traffic / (dec_launch_us * 1e-6) / 1e9
                                  if traffic is not None else None),
-                "kernel": "step_pairs_kernel", "bytes_per_launch": dbytes,
+                "kernel": "step_lanes_kernel", "bytes_per_launch": dbytes,
                 "launch_us": dec_launch_us,
                 "residency": "infinity-cache: the workload's one state is stepped K times in a "
                              "row and stays in the 256 MB cache; counters include cache hits"}
@@ -971,7 +970,7 @@ def main():
         traffic_pool = counter_traffic(f"decode_step_{w.name}_pool_counters.txt", dig)
         roofline = {"bound": "hbm", "achieved": streaming["gbps"], "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": streaming["frac"], "traffic": traffic_pool,
-                    "kernel": "step_pairs_kernel", "bytes_per_launch": dbytes,
+                    "kernel": "step_lanes_kernel", "bytes_per_launch": dbytes,
                     "launch_us": streaming["launch_us"],
                     "copy_floor_us": streaming["copy_floor_us"],
                     "inplace_add_floor_us": streaming["inplace_add_floor_us"],

@@ -116,11 +116,14 @@ size_t lh_prefill_workspace_bytes(int64_t B, int64_t D, int64_t d, int64_t T);
  *                   on entry are ignored and on exit undefined.
  *
  * The library picks the plan (lh_prefill_plan with plan = LH_PREFILL_AUTO
- * reports which): the matrix-core chunked scan over the whole prompt where
- * its workgroups fill the GPU, the segmented matrix-core plan where the
- * prompt must be split in time to fill it, else the VALU chunked scan (see
+ * reports which): the matrix-core plan over the whole prompt where its
+ * workgroups fill the GPU, the segmented matrix-core plan where the prompt
+ * must be split in time to fill it, else the general chunked scan, which runs
+ * on the matrix cores too where its sizes allow and that is faster (see
  * lh_prefill_with_plan for what each computes and needs).  Every plan gives
- * the same results up to float32 rounding.
+ * the same results up to float32 rounding.  On the matrix cores an input that
+ * is not finite makes the outputs of its (row, channel) from the start of its
+ * 16-step chunk on not finite.
  * T == 0 zeroes the state and leaves y untouched.  y must not overlap u,
  * state, lambda, R, h0 or workspace; state must not overlap any input.
  */
@@ -158,18 +161,16 @@ lh_status lh_prefill_noalloc(const lh_c32* lambda, const lh_c32* R, const float*
 
 /* Prefill plans (what a prefill runs). */
 typedef enum {
-    LH_PLAN_SCAN = 0,      /* VALU scan: one sequential pass or parallel time chunks */
+    LH_PLAN_SCAN = 0,      /* general chunked scan: on the matrix cores or the VALU */
     LH_PLAN_MFMA = 1,      /* matrix-core plan over the whole prompt */
     LH_PLAN_MFMA_SEG = 2   /* segmented matrix-core plan */
 } lh_prefill_plan_kind;
 
 /*
- * The plan a prefill takes for these sizes, plan request and input type when
- * u and y are 16-byte aligned (automatic matrix-core plans run the VALU scan,
- * with the same workspace, when they are not).  Returns an
- * lh_prefill_plan_kind, or -1 when the arguments are invalid or no plan
- * exists (as the prefill would fail).  Pure function of its arguments; host
- * only, no device call.
+ * The plan a prefill takes for these sizes, plan request and input type.
+ * Returns an lh_prefill_plan_kind, or -1 when the arguments are invalid or no
+ * plan exists (as the prefill would fail).  Pure function of its arguments;
+ * host only, no device call.
  */
 int lh_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t plan,
                     lh_dtype io_dtype);
@@ -192,32 +193,40 @@ size_t lh_prefill_with_plan_workspace_bytes(int64_t B, int64_t D, int64_t d, int
  *            chunk's end state from zero, a carry across chunks with
  *            lambda^plan formed in float64, then the outputs from each chunk's
  *            entry state; plan >= T means one sequential pass per row);
- *   plan = LH_PREFILL_MFMA: the matrix-core plan (chunks of 32 steps as dense
+ *   plan = LH_PREFILL_MFMA: the matrix-core plan (chunks of 16 steps as dense
  *            contractions on the MFMA units: outputs Y = T U + W X_in, chunk
- *            end states S = P U and the carry X_in <- lambda^32 X_in + S; with
+ *            end states S = P U and the carry X_in <- lambda^16 X_in + S; the
+ *            16 columns of a product are batch rows, or fewer rows and several
+ *            chunks of each; with
  *            the float32 operands split into bfloat16 terms: three with
  *            float32 u/y, two for the outputs and three for the state with
  *            bfloat16 u/y; d = 16 or 32 require D % 8 == 0, d = 64 requires
  *            float32 u/y and D % 4 == 0; always T >= 1 and 16-byte aligned u and
- *            y, else LH_ERR_INVALID_ARG).  The automatic plan uses it where
+ *            y, else LH_ERR_INVALID_ARG).  The automatic plan, which takes any
+ *            alignment of u and y, uses it where
  *            supported and either ceil(D/16) * ceil(B/32) >= 256 (enough
  *            workgroups to fill the GPU without splitting the prompt in time)
- *            or an estimate of the chunk steps each compute unit walks puts
- *            it within 7/5 of the segmented plan below (the estimate depends
+ *            or a count of the 32-step chunks each compute unit walks puts
+ *            it within 7/5 of the segmented plan below (the count depends
  *            on the input type, so float32 and bfloat16 calls may take
  *            different plans); at d = 64 also when T does not split into
  *            segments and B >= 4 or ceil(D/4) * ceil(B/16) >= 256, and never
- *            when B < 4 and B * T <= 1024 (the VALU scan is faster there);
- *   plan = LH_PREFILL_MFMA_SEG: the segmented matrix-core plan: the prompt is
- *            cut into 2^k segments of T / 2^k steps (a multiple of 32, at
- *            least 256), the fewest whose (batch row, segment) pairs fill the
- *            GPU; a matrix-core pass computes each segment's end state from
+ *            when B < 4 and B * T <= 1024;
+ *   plan = LH_PREFILL_MFMA_SEG: the segmented matrix-core plan: its workspace
+ *            holds the states of 2^k segments of T / 2^k steps (a multiple of
+ *            32, at least 256), the fewest whose (batch row, segment) pairs
+ *            fill the GPU.  The prompt is cut into at most that many where the
+ *            chunks of a row side by side in a product do not fill the GPU
+ *            already: a matrix-core pass computes each segment's end state from
  *            zero, a carry gives each segment its entry state, and a second
  *            matrix-core pass computes the outputs (same operand splitting
  *            and requirements as LH_PREFILL_MFMA, and such a T).  The
  *            automatic plan takes it where the whole-prompt matrix-core plan
  *            is supported but not chosen and T splits this way (at d = 64
  *            only when B * T > 1024).
+ * Elsewhere an automatic call runs the general chunked scan: the matrix-core
+ * pass above where d <= 64 and a fitted estimate of both times favours it, else,
+ * or with a workspace that holds only the VALU scan's states, the VALU scan.
  * workspace: at least lh_prefill_with_plan_workspace_bytes(B,D,d,T,plan)
  * bytes.  A plan request the sizes do not support returns LH_ERR_INVALID_ARG.
  */

@@ -37,6 +37,7 @@ struct MfmaCut {
     int nseg;         // segments of the prompt (1: the whole prompt in one pass)
     int64_t seg_len;  // steps per segment (a multiple of 256 when nseg > 1)
     int64_t tiles;    // estimated time, in tiles of the busiest CU
+    bool two_terms = false;  // float32 d = 16, 32, 64: entry states in two bfloat16 terms
 };
 
 // How the prefill of one call is cut up.

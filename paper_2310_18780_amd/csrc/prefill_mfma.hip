@@ -358,6 +358,7 @@ hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool
     a.D = int(D);
     a.d = int(d);
     a.nseg = cut.nseg;
+    a.two_terms = cut.two_terms;
     return bf16_io ? launch_mfma_kernel_bf16(modes16(d), cut.s, outputs, a, stream)
                    : launch_mfma_kernel_f32(modes16(d), cut.s, outputs, a, stream);
 }

@@ -40,6 +40,7 @@ struct MfmaArgs {
     float2* xs;        // segment states [B, nseg, D, d]
     int64_t T, seg_len;
     int B, D, d, nseg;
+    bool two_terms;     // MfmaCut
     int ncg, nrg, per_xcd;  // grid (set by the launcher)
 };
 

@@ -645,7 +645,7 @@ hipError_t launch_dm(int s, bool outputs, const MfmaArgs& a, hipStream_t stream)
 {
     if (!outputs) return launch_tiled<IO, DM, 16, false, false>(a, stream);
     if constexpr (sizeof(IO) == 4 && DM != 3)
-        if (a.d == 16 * DM) return launch_s<IO, DM, true>(s, a, stream);
+        if (a.two_terms && a.d == 16 * DM) return launch_s<IO, DM, true>(s, a, stream);
     return launch_s<IO, DM, false>(s, a, stream);
 }
 
