@@ -49,6 +49,8 @@
 //
 // Both finalise the gradients without dividing by lambda, so A = 0 is exact.  The
 // traffic is the target read once.
+#include <type_traits>
+
 #include "lh_internal.hpp"
 
 namespace lh {
@@ -323,6 +325,13 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
 #pragma unroll
         for (int z = 0; z < 4; ++z) F[m][z] = f32x4{0.f, 0.f, 0.f, 0.f};
     float lacc = 0.f;
+    // Rows of a tile that take part in F: not a = 0 (added at the end), and not those
+    // past the last tap, whose powers may overflow where |lambda| > 1 while every
+    // power up to lambda^(L-1) is finite (inf times the zero errors there is no zero).
+    auto inside = [&](int64_t s0, int i) {
+        const int64_t s = s0 + 16 * (4 * i + g);
+        return s > 0 && s < L;
+    };
 
     for (int64_t k0 = 0; k0 < ntile; k0 += kMaxTiles) {
         const int nk = int(ntile - k0 < kMaxTiles ? ntile - k0 : kMaxTiles);
@@ -361,35 +370,46 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
                 e0_s[q] = e[0];
                 e[0] = 0.f;
             }
+            auto accumulate = [&](auto edge) {
 #pragma unroll
-            for (int m = 0; m < DM; ++m) {
-                const float2 a = wk[k + 1][16 * m + q], a0 = wk[k + (g > 0)][16 * m + q];
+                for (int m = 0; m < DM; ++m) {
+                    const float2 a = wk[k + 1][16 * m + q], a0 = wk[k + (g > 0)][16 * m + q];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float2 p = cmul(P1[m][i], i == 0 ? a0 : a);
-                    F[m][0] = mfma4(p.x, e[i], F[m][0]);
-                    F[m][1] = mfma4(p.y, e[i], F[m][1]);
-                    F[m][2] = mfma4(p.x, ae[i], F[m][2]);
-                    F[m][3] = mfma4(p.y, ae[i], F[m][3]);
+                    for (int i = 0; i < 4; ++i) {
+                        float2 p = cmul(P1[m][i], i == 0 ? a0 : a);
+                        if constexpr (decltype(edge)::value)
+                            if (!inside(s0, i)) p = make_float2(0.f, 0.f);
+                        F[m][0] = mfma4(p.x, e[i], F[m][0]);
+                        F[m][1] = mfma4(p.y, e[i], F[m][1]);
+                        F[m][2] = mfma4(p.x, ae[i], F[m][2]);
+                        F[m][3] = mfma4(p.y, ae[i], F[m][3]);
+                    }
                 }
-            }
+            };
+            if (s0 == 0 || s0 + kTile > L)  // (in every tile the masks take 1 of the 30 us)
+                accumulate(std::true_type{});
+            else
+                accumulate(std::false_type{});
         }
     }
 
-    // F = lambda^16 F1 + e[0], sums over b, then over the waves
+    // F = lambda^16 F1 + e[0], sums over b, then over the waves; powers that no tap
+    // has stay out here too
     __syncthreads();
     const float e0 = w == 0 ? e0_s[q] : 0.f;
     const float fb = float(q);
+    const float2 none = make_float2(0.f, 0.f);
+    const bool rows = L > 16;  // any a > 0
 #pragma unroll
     for (int m = 0; m < DM; ++m)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int n = 16 * m + 4 * g + i;
-            const float2 p = pw[n][q];                                        // lambda^b
-            const float2 pb = q > 0 ? pw[n][q - 1] : make_float2(0.f, 0.f);  // lambda^(b-1)
-            float2 f = cmul(p16[n][1], make_float2(F[m][0][i], F[m][1][i]));
+            const float2 p = q < L ? pw[n][q] : none;               // lambda^b
+            const float2 pb = q > 0 && q < L ? pw[n][q - 1] : none;  // lambda^(b-1)
+            float2 f = rows ? cmul(p16[n][1], make_float2(F[m][0][i], F[m][1][i])) : none;
             f.x += e0;
-            const float2 fd = cmul(pw[n][15], make_float2(F[m][2][i], F[m][3][i]));
+            const float2 fd = rows ? cmul(pw[n][15], make_float2(F[m][2][i], F[m][3][i])) : none;
             const float2 gv = cmul(p, f);
             const float2 s1 = cmul(p, fd), s2 = cmul(pb, f);
             const float v0 = row_sum16(gv.x), v1 = row_sum16(gv.y);

@@ -156,3 +156,16 @@ def test_tile_edges(case):
     A[0, 0] = 0.0
     tgt = workloads.distill_target(w, L, tau=max(8.0, L / 8))
     compare(run_gpu(A, th, R, tgt), od.distill_loss_grad(A, th, R, tgt), str(case))
+
+
+@pytest.mark.parametrize("a,L", [(1.45, 90), (8.0, 17), (8.0, 16), (500.0, 6)], ids=str)
+def test_growing_powers(a, L):
+    """|lambda| > 1 where every power up to lambda^(L-1) is finite while powers further
+    on in the same tile of 256 taps (lambda^240; at 500 lambda^15) are not."""
+    _log(f"distill growing a={a} L={L}")
+    (A, th, R), w = params(3, 18, seed=13)
+    A = A.copy()
+    A[0, 0] = A[1, 5] = A[1, 17] = A[2, 16] = a
+    assert 240 * math.log10(a) > 38.6  # past float32
+    tgt = workloads.distill_target(w, L, tau=max(8.0, L / 8))
+    compare(run_gpu(A, th, R, tgt), od.distill_loss_grad(A, th, R, tgt), f"{a} {L}")
