@@ -426,17 +426,22 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
     __syncthreads();
     if (tid == 0) loss[c] = (loss_s[0] + loss_s[1]) + (loss_s[2] + loss_s[3]);
     if (tid < d) {
-        float v[4];
+        // in float64, once per mode: R S lambda is almost real where one mode explains
+        // the error of its taps, and its imaginary part, the gradient in theta, then
+        // keeps every rounding of the product
+        double v[4];
 #pragma unroll
         for (int z = 0; z < 4; ++z)
-            v[z] = (red[0][tid][z] + red[1][tid][z]) + (red[2][tid][z] + red[3][tid][z]);
-        const float2 r = Rc[tid], lam = pw[tid][1];
-        const double th = Tc[tid];
-        const float2 unit = make_float2(float(cos(th)), float(sin(th)));
-        const float2 rs = cmul(r, make_float2(v[2], v[3]));
-        dR[int64_t(c) * d + tid] = make_float2(2.f * v[0], -2.f * v[1]);
-        dA[int64_t(c) * d + tid] = 2.f * cmul(rs, unit).x;
-        dtheta[int64_t(c) * d + tid] = -2.f * cmul(rs, lam).y;  // Re(i z) = -Im(z)
+            v[z] = (double(red[0][tid][z]) + red[1][tid][z]) + (double(red[2][tid][z]) + red[3][tid][z]);
+        const float2 r = Rc[tid];
+        const double a = Ac[tid], th = Tc[tid];
+        double sn, cs;
+        sincos(th, &sn, &cs);
+        const double rx = double(r.x) * v[2] - double(r.y) * v[3];
+        const double ry = double(r.x) * v[3] + double(r.y) * v[2];
+        dR[int64_t(c) * d + tid] = make_float2(float(2.0 * v[0]), float(-2.0 * v[1]));
+        dA[int64_t(c) * d + tid] = float(2.0 * (rx * cs - ry * sn));
+        dtheta[int64_t(c) * d + tid] = float(-2.0 * a * (rx * sn + ry * cs));  // Re(i z) = -Im(z)
     }
 }
 

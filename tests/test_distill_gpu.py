@@ -169,3 +169,20 @@ def test_growing_powers(a, L):
     assert 240 * math.log10(a) > 38.6  # past float32
     tgt = workloads.distill_target(w, L, tau=max(8.0, L / 8))
     compare(run_gpu(A, th, R, tgt), od.distill_loss_grad(A, th, R, tgt), f"{a} {L}")
+
+
+def test_cancelling_pole_gradients():
+    """One mode fitted to a target of zeros: 2 R S lambda is almost real, so that the
+    gradient in theta is 1e-2 .. 1e-4 of its magnitude and shows the rounding of the
+    products in float32 that form it (2^-24 each on either component, several of them);
+    formed in float64 from the sums it keeps only the errors of those."""
+    D, L = 512, 4096
+    w = workloads.Workload("case", 1, D, 1, 1, 1, "f32", 0.99, 0.9999, math.pi, 1.0, 17)
+    A, th, R = workloads.distill_params(w)
+    tgt = np.zeros((D, L), np.float32)
+    ref = od.distill_loss_grad(A, th, R, tgt)
+    got = run_gpu(A, th, R, tgt, want_h=False)
+    size = np.hypot(ref["dA"], ref["dtheta"] / A)
+    err = [float(np.sqrt(np.mean(((got[k] - ref[k]) / size) ** 2))) for k in ("dA", "dtheta")]
+    _log(f"cancelling pole gradients {err} {np.median(np.abs(ref['dtheta']) / size)}")
+    assert err[1] <= 2.0 ** -25, err
