@@ -198,8 +198,8 @@ lh_status check_prefill_buffers(const lh_c32* lambda, const lh_c32* R, const flo
     return LH_OK;
 }
 
-// A scan runs on the matrix cores where its sizes allow; with less workspace than
-// their tables need it runs on the VALU, as with exactly the VALU scan's size.
+// A scan runs on the matrix cores where its sizes allow; without a workspace that
+// holds their tables it runs on the VALU, as with exactly the VALU scan's size.
 void use_scan(lh::PrefillPlan* p)
 {
     p->mfma = false;
@@ -319,10 +319,18 @@ lh_status lh_prefill_with_plan(const lh_c32* lambda, const lh_c32* R, const floa
                            reinterpret_cast<uintptr_t>(y) % 16 != 0))
         return fail(LH_ERR_INVALID_ARG, "the matrix-core plan needs 16-byte aligned u and y");
 
-    if (pl.named == LH_PLAN_SCAN && workspace_bytes < pl.ws_bytes) use_scan(&pl);
-    if ((s = check_prefill_buffers(lambda, R, h0, u, B, D, d, T, io_dtype, state, y, workspace,
-                                   pl.ws_bytes, workspace_bytes)) != LH_OK)
-        return s;
+    s = check_prefill_buffers(lambda, R, h0, u, B, D, d, T, io_dtype, state, y, workspace,
+                              pl.ws_bytes, workspace_bytes);
+    if (s != LH_OK && pl.named == LH_PLAN_SCAN && pl.mfma) {
+        // Whatever is wrong with the workspace as the tables' (too small, missing,
+        // misaligned, overlapping), it may be one that the VALU scan takes, which
+        // needs less or none.
+        use_scan(&pl);
+        s = check_prefill_buffers(lambda, R, h0, u, B, D, d, T, io_dtype, state, y, workspace,
+                                  pl.ws_bytes, workspace_bytes);
+        if (s == LH_OK) g_last_error[0] = '\0';
+    }
+    if (s != LH_OK) return s;
 
     return from_hip(
         lh::launch_prefill(reinterpret_cast<const float2*>(lambda),

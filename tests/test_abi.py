@@ -235,6 +235,25 @@ def test_valid_arguments_report_no_device_without_gpu():
     assert L.lh_step(*step_args(io=lh.LH_BF16)) == 4
 
 
+@pytest.mark.parametrize("ws,ws_bytes", [
+    (None, 0), (None, 1 << 40), (A + 9 * MB + 8, 1 << 40),  # missing, misaligned,
+    (A + 1000 * MB, 1 << 40), (A + 4000 * MB, 256),         # over y, too small
+])
+def test_scan_sizes_take_any_workspace_that_the_valu_scan_takes(ws, ws_bytes):
+    """Sizes that a single VALU pass serves without a workspace take the matrix cores
+    when the workspace holds their tables; any other workspace argument, which the
+    VALU scan does not look at, is still accepted."""
+    if not no_gpu():
+        pytest.skip("made-up addresses are only passed through when no GPU is visible")
+    B, D, d, T = 64, 2048, 12, 256
+    assert lh.workspace_bytes(B, D, d, T, plan=T) == 0 < lh.workspace_bytes(B, D, d, T)
+    L = lh.lib()
+    kw = dict(B=B, D=D, d=d, T=T, u=A + 100 * MB, state=A + 500 * MB, y=A + 1000 * MB, ws=ws,
+              ws_bytes=ws_bytes)
+    assert L.lh_prefill(*auto_args(**kw)) == 4  # reaches the device check
+    assert L.lh_prefill(*auto_args(**dict(kw, y=A + 500 * MB))) == 2  # still an overlap
+
+
 def test_binding_raises_when_library_missing(monkeypatch, tmp_path):
     monkeypatch.setattr(lh, "_LIB_PATH", str(tmp_path / "missing.so"))
     monkeypatch.setattr(lh, "_lib", None)
