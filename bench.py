@@ -154,11 +154,11 @@ def mfma64_flops(w):
     return 16384 * w.D * -(-w.B // 16) * 43 * -(-w.T // 16)
 
 
-def dtype_detail(w, plan):
+def dtype_detail(w, path):
     """What the arithmetic of the path is, beyond the float32 label."""
     io = "bfloat16 u/y (widened exactly, outputs rounded to nearest even)" if w.io == "bf16" \
         else "float32 u/y"
-    if plan == "scan":
+    if path == "valu":
         pre = "prefill on the float32 VALU"
     elif w.io == "bf16":
         pre = ("prefill contractions on bfloat16 matrix cores with float32 accumulation: "
@@ -896,11 +896,11 @@ def main():
     # u and y, d = 32 with bfloat16 u and y, against 2500 / 8 = 312), so their
     # roofline is HBM; at d = 64 the 43 products per channel, 16 columns and 16
     # steps come to 344 flops per byte, above the ridge, so its roofline is the
-    # bfloat16 MFMA peak; the general scan (plan "scan") is held against the VALU
-    # peak, which its declared flops reach on the VALU.
+    # bfloat16 MFMA peak; the VALU scan is held against the VALU peak.
     plan = lh.prefill_plan(w.B, w.D, w.d, w.T, io=w.io)
+    path, columns, segments = lh.prefill_path(w.B, w.D, w.d, w.T, io=w.io)
     pre_gbs = prefill_bytes(w) / (pre_avg * 1e-3) / 1e9
-    if plan == "scan":
+    if path == "valu":
         roofline_prefill = {"bound": "alu", "achieved": pre_tf, "peak": FP32_VALU_PEAK_TFLOPS,
                             "unit": "TFLOP/s", "frac": pre_tf / FP32_VALU_PEAK_TFLOPS}
     elif w.d == 64:  # matrix-core plan above the MFMA ridge: bound by the bf16 MFMA rate
@@ -913,7 +913,8 @@ def main():
         roofline_prefill = {"bound": "hbm", "achieved": pre_gbs, "peak": HBM_PEAK_GBS,
                             "unit": "GB/s", "frac": pre_gbs / HBM_PEAK_GBS}
     roofline_prefill.update({
-        "plan": plan, "traffic": traffic_pre,
+        "plan": plan, "path": path, "columns_per_row": columns, "segments": segments,
+        "traffic": traffic_pre,
         "traffic_gbps": (traffic_pre / (pre_avg * 1e-3) / 1e9 if traffic_pre is not None else None),
         "flops_per_launch": prefill_flops(w), "bytes_per_launch": prefill_bytes(w),
         "gbps": pre_gbs, "declared_tflops": pre_tf,
@@ -992,7 +993,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
-        "dtype_detail": dtype_detail(w, plan),
+        "dtype_detail": dtype_detail(w, path),
         "data": "synthetic",
         "config": {"workload": w.name, "B": B, "D": D, "d": d, "T": T, "K": K, "io": w.io,
                    "decode_launch": args.decode_launch, "prefill_workspace_bytes": wsb},

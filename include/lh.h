@@ -159,21 +159,38 @@ lh_status lh_prefill_noalloc(const lh_c32* lambda, const lh_c32* R, const float*
 #define LH_PREFILL_MFMA (-1)
 #define LH_PREFILL_MFMA_SEG (-2)
 
-/* Prefill plans (what a prefill runs). */
+/* Prefill plans: names that fix a call's workspace.  lh_prefill_path tells what
+ * runs inside it. */
 typedef enum {
-    LH_PLAN_SCAN = 0,      /* general chunked scan: on the matrix cores or the VALU */
+    LH_PLAN_SCAN = 0,      /* general chunked scan */
     LH_PLAN_MFMA = 1,      /* matrix-core plan over the whole prompt */
     LH_PLAN_MFMA_SEG = 2   /* segmented matrix-core plan */
 } lh_prefill_plan_kind;
 
 /*
- * The plan a prefill takes for these sizes, plan request and input type.
+ * The plan of a prefill with these sizes, plan request and input type.
  * Returns an lh_prefill_plan_kind, or -1 when the arguments are invalid or no
  * plan exists (as the prefill would fail).  Pure function of its arguments;
  * host only, no device call.
  */
 int lh_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t plan,
                     lh_dtype io_dtype);
+
+/*
+ * What such a call executes with a workspace of at least
+ * lh_prefill_with_plan_workspace_bytes bytes and 16-byte aligned u and y.
+ * Returns 1 for the matrix cores, 0 for the VALU scan, -1 where
+ * lh_prefill_plan does.  *columns (unless NULL): on the matrix cores the
+ * consecutive 16-step chunks of a row that a product takes side by side (1, 2, 4
+ * or 16 of its 16 columns), else 1.  *segments (unless NULL): the time segments
+ * processed in parallel (1: the prompt in one pass).  The name of a plan does not
+ * tell: the scan runs on the matrix cores where that is the faster way, a
+ * whole-prompt plan may be cut into segments and a segmented one may not, and
+ * past 2^31 bytes in 257 steps of a row every plan runs on the VALU.  Pure
+ * function of its arguments; host only, no device call.
+ */
+int lh_prefill_path(int64_t B, int64_t D, int64_t d, int64_t T, int64_t plan,
+                    lh_dtype io_dtype, int64_t* columns, int64_t* segments);
 
 /*
  * Workspace bytes of lh_prefill_with_plan for this plan request (as

@@ -6,7 +6,8 @@ calls the library.  Every step of the computation runs in the library's HIP
 kernels; there is no fallback.  PyTorch provides device memory and streams.
 
     prefill(lam, R, h0, u, state, y)   # y[b,t,c], t < T, and state = x_T
-    prefill_plan(B, D, d, T, io="bf16")  # which plan prefill takes ("scan", "mfma", "mfma_seg")
+    prefill_plan(B, D, d, T, io="bf16")  # its plan's name ("scan", "mfma", "mfma_seg")
+    prefill_path(B, D, d, T, io="bf16")  # what runs: ("mfma" or "valu", columns, segments)
     prefill_with_plan(lam, R, h0, u, state, y, plan=PLAN_MFMA)  # a named plan (tests, benchmarks)
     prefill_fft(lam, R, h0, u, state, y)  # the same results by FFT convolution
     step(lam, R, h0, state, u_t, y_t)  # y_t from x_t, then x_{t+1} in place
@@ -29,6 +30,7 @@ __all__ = [
     "library_path",
     "workspace_bytes",
     "prefill_plan",
+    "prefill_path",
     "PREFILL_PLANS",
     "PLAN_AUTO",
     "PLAN_MFMA",
@@ -118,6 +120,9 @@ def lib() -> ctypes.CDLL:
     L.lh_prefill_with_plan_workspace_bytes.restype = sz
     L.lh_prefill_plan.argtypes = [i64, i64, i64, i64, i64, ctypes.c_int]
     L.lh_prefill_plan.restype = ctypes.c_int
+    L.lh_prefill_path.argtypes = [i64, i64, i64, i64, i64, ctypes.c_int, ctypes.POINTER(i64),
+                                  ctypes.POINTER(i64)]
+    L.lh_prefill_path.restype = ctypes.c_int
     L.lh_prefill.argtypes = [vp, vp, vp, vp, i64, i64, i64, i64, ctypes.c_int, vp, vp, vp, sz, vp]
     L.lh_prefill.restype = ctypes.c_int
     L.lh_prefill_with_plan.argtypes = [vp, vp, vp, vp, i64, i64, i64, i64, ctypes.c_int, vp, vp,
@@ -175,12 +180,24 @@ PREFILL_PLANS = ("scan", "mfma", "mfma_seg")
 
 
 def prefill_plan(B: int, D: int, d: int, T: int, plan: int = PLAN_AUTO, io: str = "f32") -> str:
-    """The plan a prefill takes for 16-byte aligned u and y (``lh_prefill_plan``):
-    "scan" (VALU), "mfma" (matrix cores, whole prompt) or "mfma_seg" (segmented)."""
+    """The name of a prefill's plan, which fixes its workspace (``lh_prefill_plan``):
+    "scan", "mfma" (matrix cores, whole prompt) or "mfma_seg" (segmented).
+    ``prefill_path`` tells what runs."""
     k = lib().lh_prefill_plan(B, D, d, T, plan, {"f32": 0, "bf16": 1}[io])
     if k < 0:
         raise LHError(1, f"no prefill plan for B={B} D={D} d={d} T={T} plan={plan} io={io}")
     return PREFILL_PLANS[k]
+
+
+def prefill_path(B: int, D: int, d: int, T: int, plan: int = PLAN_AUTO, io: str = "f32"):
+    """What a prefill executes (``lh_prefill_path``): ("mfma" or "valu", chunks of a
+    row side by side in a matrix product, time segments in parallel)."""
+    columns, segments = ctypes.c_int64(), ctypes.c_int64()
+    k = lib().lh_prefill_path(B, D, d, T, plan, {"f32": 0, "bf16": 1}[io], ctypes.byref(columns),
+                              ctypes.byref(segments))
+    if k < 0:
+        raise LHError(1, f"no prefill plan for B={B} D={D} d={d} T={T} plan={plan} io={io}")
+    return ("valu", "mfma")[k], columns.value, segments.value
 
 
 def _io_dtype(t) -> int:

@@ -290,6 +290,19 @@ int lh_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t plan, lh
     return p.named;
 }
 
+int lh_prefill_path(int64_t B, int64_t D, int64_t d, int64_t T, int64_t plan, lh_dtype io_dtype,
+                    int64_t* columns, int64_t* segments)
+{
+    if (check_sizes(B, D, d, T) != LH_OK || plan < LH_PREFILL_MFMA_SEG ||
+        (io_dtype != LH_F32 && io_dtype != LH_BF16))
+        return -1;
+    lh::PrefillPlan p;
+    if (!lh::make_prefill_plan(B, D, d, T, plan, io_dtype == LH_BF16 ? 1 : 0, &p)) return -1;
+    if (columns) *columns = p.mfma ? p.cut.s : 1;
+    if (segments) *segments = p.mfma ? p.cut.nseg : p.nchunks > 1 ? p.nchunks : 1;
+    return p.mfma;
+}
+
 lh_status lh_prefill_with_plan(const lh_c32* lambda, const lh_c32* R, const float* h0,
                                const void* u, int64_t B, int64_t D, int64_t d, int64_t T,
                                lh_dtype io_dtype, lh_c32* state, void* y, int64_t plan,

@@ -149,6 +149,29 @@ def test_prefill_plan_query():
         assert L.lh_prefill_plan(*args) == -1, args
 
 
+def test_prefill_path_query():
+    """lh_prefill_path: what runs, which the plan's name does not tell (host only)."""
+    P = lh.prefill_path
+    assert P(64, 2048, 16, 4096, io="bf16") == ("mfma", 1, 1)
+    assert P(1, 768, 16, 512) == ("mfma", 16, 1)
+    assert lh.prefill_plan(4, 1024, 32, 65536) == "mfma_seg"   # its workspace, in one pass
+    assert P(4, 1024, 32, 65536) == ("mfma", 16, 1)
+    assert lh.prefill_plan(7, 1000, 12, 1999, io="bf16") == "scan"
+    assert P(7, 1000, 12, 1999, io="bf16")[0] == "mfma"
+    assert P(7, 1000, 12, 1999, plan=500) == ("valu", 1, 4)
+    assert P(2, 70, 65, 300)[0] == "valu"                      # more than 64 modes
+    assert P(3, 8, 4, 0) == ("valu", 1, 1)
+    wide = 1 << 23                                             # 2^31 bytes in 64 steps
+    assert lh.prefill_plan(1, wide, 16, 32, plan=-1) == "mfma"
+    assert P(1, wide, 16, 32, plan=-1)[0] == "valu"
+    ws = lh.workspace_bytes(1, wide, 16, 32, plan=-1)
+    assert ws >= lh.workspace_bytes(1, wide, 16, 32, plan=32)  # holds the scan that runs
+    L = lh.lib()
+    assert L.lh_prefill_path(2, 16, 16, 64, -1, 0, None, None) == 1
+    for args in [(2, 12, 16, 64, -1, 0), (0, 1, 1, 1, 0, 0), (1, 1, 1, 1, -3, 0), (1, 1, 1, 1, 0, 2)]:
+        assert L.lh_prefill_path(*args, None, None) == -1, args
+
+
 # made-up, well-separated, aligned addresses (never dereferenced)
 A = 0x7F0000000000
 MB = 1 << 20

@@ -22,25 +22,25 @@ from parity_util import BF16_REL, REL_TOL, to_device
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (B, D, d, T, io); chunks per row among the columns by the rule of the cut
-    (60, 1022, 12, 100, "f32"),   # 1: partial chunk, D % 16 != 0, ragged rows
-    (50, 2035, 7, 83, "bf16"),    # 1: D odd
-    (33, 1100, 30, 95, "f32"),    # 1, two sixteens of modes
-    (45, 1030, 24, 70, "bf16"),   # 1
-    (17, 1203, 45, 66, "f32"),    # 2: three sixteens
-    (40, 600, 60, 130, "bf16"),   # 1: four sixteens
-    (19, 530, 61, 71, "f32"),     # 2
-    (9, 1030, 12, 250, "f32"),    # 4
-    (23, 1500, 16, 301, "bf16"),  # 2
-    (12, 700, 20, 520, "f32"),    # 4
-    (5, 530, 40, 333, "bf16"),    # 4
-    (3, 101, 5, 1000, "f32"),     # 16
-    (2, 36, 48, 513, "f32"),
-    (1, 64, 12, 16 * 1024 + 9, "f32"),   # segments, the last one partial
-    (2, 72, 17, 8192 + 256, "bf16"),     # segments, the last one of one tile
-    (1, 24, 33, 5000, "f32"),
-    (6, 4, 64, 300, "bf16"),      # one piece of channels
-    (300, 18, 33, 200, "f32"),    # half a channel group, whole pieces
+    # (B, D, d, T, io, chunks per row among the columns, segments)
+    (60, 1022, 12, 100, "f32", 1, 1),   # partial chunk, D % 16 != 0, ragged rows
+    (50, 2035, 7, 83, "bf16", 1, 1),    # D odd
+    (33, 1100, 30, 95, "f32", 1, 1),    # 1, two sixteens of modes
+    (45, 1030, 24, 70, "bf16", 1, 1),
+    (17, 1203, 45, 66, "f32", 2, 1),    # three sixteens
+    (40, 600, 60, 130, "bf16", 1, 1),   # four sixteens
+    (19, 530, 61, 71, "f32", 2, 1),
+    (9, 1030, 12, 250, "f32", 4, 1),
+    (23, 1500, 16, 301, "bf16", 2, 1),
+    (12, 700, 20, 520, "f32", 4, 1),
+    (5, 530, 40, 333, "bf16", 4, 1),
+    (3, 101, 5, 1000, "f32", 16, 1),
+    (2, 36, 48, 513, "f32", 16, 1),
+    (1, 64, 12, 16 * 1024 + 9, "f32", 16, 33),   # the last one partial
+    (2, 72, 17, 8192 + 256, "bf16", 16, 17),     # the last one of one tile
+    (1, 24, 33, 5000, "f32", 16, 10),
+    (6, 4, 64, 300, "bf16", 16, 1),      # one piece of channels
+    (300, 18, 33, 200, "f32", 4, 1),    # half a channel group, whole pieces
 ]
 
 
@@ -90,18 +90,18 @@ def _same(a, b, io):
     assert bool((xerr <= 2 * REL_TOL * xb.abs().amax(dim=2, keepdim=True)).all())
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "B%d_D%d_d%d_T%d_%s" % c)
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "B%d_D%d_d%d_T%d_%s" % c[:5])
 def test_against_the_scan(case):
     import torch
 
     import paper_2310_18780_amd as lh
 
-    B, D, d, T, io = case
-    (lam, R, h0), t, u = _inputs(*case, seed=B * 1000 + d)
+    B, D, d, T, io, *cut = case
+    (lam, R, h0), t, u = _inputs(*case[:5], seed=B * 1000 + d)
     print(f"[columns] {case}", flush=True)
     auto = _run(lambda x, y: lh.prefill(t["lam"], t["R"], t["h0"], u, x, y), u, d)
     scan = _run(lambda x, y: lh.prefill_with_plan(t["lam"], t["R"], t["h0"], u, x, y, T), u, d)
-    assert not torch.equal(auto[1], scan[1])  # the automatic choice is not the scan
+    assert lh.prefill_path(B, D, d, T, io=io) == ("mfma", *cut)
     _same(auto, scan, io)
     rows = [(B - 1, D - 1), (B // 2, D // 3)]
     up = u.float().cpu().numpy()
@@ -163,7 +163,7 @@ def test_error_is_the_scans(case):
     print(f"[error] {case}", flush=True)
     auto = _run(lambda x, y: lh.prefill(t["lam"], t["R"], t["h0"], u, x, y), u, d)
     scan = _run(lambda x, y: lh.prefill_with_plan(t["lam"], t["R"], t["h0"], u, x, y, T), u, d)
-    assert not torch.equal(auto[1], scan[1])
+    assert lh.prefill_path(B, D, d, T)[0] == "mfma"
     k = torch.arange(T - 1, device="cuda", dtype=torch.float64)
     h = torch.empty((T, D), dtype=torch.float64, device="cuda")
     h[0] = t["h0"].double()
