@@ -33,11 +33,11 @@ __device__ __forceinline__ void io_store_nt(bf16* p, float v) {
 
 // Columns and segments of a matrix-core prefill.
 struct MfmaCut {
-    int s;            // time chunks per row among the kernel's 16 columns (2, 4 or 16)
+    int s;            // time chunks per row among the kernel's 16 columns (1, 2, 4 or 16)
     int nseg;         // segments of the prompt (1: the whole prompt in one pass)
     int64_t seg_len;  // steps per segment (a multiple of 256 when nseg > 1)
     int64_t tiles;    // estimated time, in tiles of the busiest CU
-    bool two_terms = false;  // float32 d = 16, 32, 64: entry states in two bfloat16 terms
+    bool two_terms = false;  // the two-term kernels (named plans, 16-byte aligned u and y)
 };
 
 // How the prefill of one call is cut up.
@@ -78,9 +78,9 @@ hipError_t launch_prefill(const float2* lam, const float2* R, const float* h0,
 // and sizes that the kernel takes.
 bool mfma_supported(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io);
 bool mfma_possible(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io);
-// Table bytes of the named plans (either input type) and of one input type.
+// Table bytes of the named plans (either input type) and of one input type and kernel.
 size_t mfma_workspace_bytes(int64_t D, int64_t d);
-size_t mfma_table_bytes(bool bf16_io, int64_t D, int64_t d);
+size_t mfma_table_bytes(bool bf16_io, bool two_terms, int64_t D, int64_t d);
 // Segment slots of the segmented plan's workspace (0 when T does not split into
 // segments of a multiple of 32 steps, at least 256 long).
 int64_t mfma_segments(int64_t B, int64_t D, int64_t d, int64_t T);
@@ -88,7 +88,8 @@ int64_t mfma_segments(int64_t B, int64_t D, int64_t d, int64_t T);
 MfmaCut mfma_cut(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64_t max_seg);
 // Tables of the filters into the workspace.
 hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0, int64_t D,
-                             int64_t d, bool bf16_io, void* workspace, hipStream_t stream);
+                             int64_t d, bool bf16_io, bool two_terms, void* workspace,
+                             hipStream_t stream);
 // One pass: outputs = false writes each segment's end state from zero into slot
 // k < nseg - 1 of xs [B, nseg, D, d]; outputs = true runs every segment from its
 // entry state in xs (the whole prompt from zero when nseg = 1), writes y and x_T.

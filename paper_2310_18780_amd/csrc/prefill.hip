@@ -430,7 +430,7 @@ bool make_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t reque
             const size_t off =
                 (p.off_xin + static_cast<size_t>(B) * p.cut.nseg * D * d * sizeof(float2) + 255) /
                 256 * 256;
-            if (off + mfma_table_bytes(bf, D, d) <= p.ws_bytes)
+            if (off + mfma_table_bytes(bf, true, D, d) <= p.ws_bytes)
                 p.off_mfma = off;
             else
                 p.cut = mfma_cut(B, D, d, T, bf, 1);
@@ -451,7 +451,7 @@ bool make_prefill_plan(int64_t B, int64_t D, int64_t d, int64_t T, int64_t reque
                 off = (p.off_xin + static_cast<size_t>(B) * p.cut.nseg * D * d * sizeof(float2) + 255) /
                       256 * 256;
             p.off_mfma = off;
-            p.ws_bytes = off + mfma_table_bytes(bf, D, d);
+            p.ws_bytes = off + mfma_table_bytes(bf, false, D, d);
         }
     }
     if (!p.mfma && p.ws_bytes < p.scan_bytes) p.ws_bytes = p.scan_bytes;
@@ -477,13 +477,18 @@ hipError_t launch_prefill(const float2* lam, const float2* R, const float* h0, c
         float2* lamC = reinterpret_cast<float2*>(ws + p.off_pow);
         float2* xs = reinterpret_cast<float2*>(ws + p.off_xin);
         void* mws = ws + p.off_mfma;
-        // The named plans' entry states take two terms (errors near 3e-6); where the
-        // VALU scan is what callers had (below 1e-6: other sizes, unaligned u or y), three.
+        // The named plans take two terms where their outputs allow it; where the VALU
+        // scan is what callers had (other sizes, unaligned u or y), three everywhere.
         MfmaCut cut = p.cut;
         cut.two_terms = p.named != 0 && (reinterpret_cast<uintptr_t>(u) |
                                          reinterpret_cast<uintptr_t>(y)) % 16 == 0;
+        if (!cut.two_terms &&
+            (cut.nseg > 1 ? p.off_mfma : 0) + mfma_table_bytes(bf16_io, false, D, d) > p.ws_bytes)
+            cut = mfma_cut(B, D, d, T, bf16_io, 1);  // a named plan's segments left less room
+        if (cut.nseg == 1) mws = ws;
         hipError_t e;
-        if ((e = launch_mfma_setup(lam, R, h0, D, d, bf16_io, mws, stream)) != hipSuccess) return e;
+        if ((e = launch_mfma_setup(lam, R, h0, D, d, bf16_io, cut.two_terms, mws, stream)) != hipSuccess)
+            return e;
         if (cut.nseg > 1) {
             hipLaunchKernelGGL(pow_kernel, g_pow, dim3(kBlock), 0, stream, lam, lamC, D * d,
                                cut.seg_len);

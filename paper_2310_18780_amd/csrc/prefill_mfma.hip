@@ -105,15 +105,15 @@ __device__ __forceinline__ void split3(float v, __bf16 (&t)[3])
 // forms a power by repeated squaring, and a wave forms all fragments of a matrix
 // tile from one evaluation of its values (D = 768, d = 16: 8-10 us before, 5.6-7.6 us
 // so; D = 2048, d = 64: 41 and 28 us).
-template <bool BF, int DM>
+template <bool BF, int DM, bool X3>
 __global__ __launch_bounds__(kSetupThreads) void mfma_setup_kernel(const float2* __restrict__ lam,
                                                                    const float2* __restrict__ R,
                                                                    const float* __restrict__ h0,
                                                                    int d, bf16x8* __restrict__ frag,
                                                                    float4* __restrict__ lamc)
 {
-    using Cf = MfmaTiling<BF, DM>;
-    constexpr int dp = 16 * DM, F = Cf::kFrags, NTX = BF ? 2 : 3;
+    using Cf = MfmaTiling<BF, DM, X3>;
+    constexpr int dp = 16 * DM, F = Cf::kFrags, NTW = BF && !X3 ? 2 : 3;
     __shared__ double pwr[dp][kC + 1], pwi[dp][kC + 1];
     __shared__ double rre[dp], rim[dp];
     __shared__ double taps[kC];
@@ -195,50 +195,59 @@ __global__ __launch_bounds__(kSetupThreads) void mfma_setup_kernel(const float2*
         }
         if (tile >= 2 * DM && tile < 3 * DM) {
 #pragma unroll
-            for (int k = 0; k < NTX; ++k) out[(Cf::kW + (tile - 2 * DM) * NTX + k) * 64] = t[k];
-        } else {  // [a1 | a2], then [a1 | a3], or with bfloat16 u [a3 | 0] (P only)
+            for (int k = 0; k < NTW; ++k) out[(Cf::kW + (tile - 2 * DM) * NTW + k) * 64] = t[k];
+        } else {  // [a1 | a2], then [a1 | a3], or with bfloat16 u [a3 | 0] (if T has it)
             const int f = tile < 2 * DM ? Cf::kP + 2 * tile : 0;
             const bf16x8 none = {};
             out[f * 64] = g < 2 ? t[0] : t[1];
             if (!BF) out[(f + 1) * 64] = g < 2 ? t[0] : t[2];
-            if (BF && tile < 2 * DM) out[(f + 1) * 64] = g < 2 ? t[2] : none;
+            if (BF && (X3 || tile < 2 * DM)) out[(f + 1) * 64] = g < 2 ? t[2] : none;
         }
     }
 }
 
 int modes16(int64_t d) { return int((d + 15) / 16); }
 
-size_t frag_bytes(bool bf16_io, int64_t D, int64_t d)
+size_t frag_bytes(bool bf16_io, bool two_terms, int64_t D, int64_t d)
 {
     const int dm = modes16(d);
-    return size_t(D) * size_t(bf16_io ? 1 + 6 * dm : 2 + 7 * dm) * 64 * sizeof(bf16x8);
+    return size_t(D) * size_t(bf16_io && two_terms ? 1 + 6 * dm : 2 + 7 * dm) * 64 * sizeof(bf16x8);
+}
+
+template <bool BF, int DM, bool X3>
+hipError_t launch_setup_tiled(const float2* lam, const float2* R, const float* h0, int64_t D,
+                              int64_t d, void* workspace, hipStream_t stream)
+{
+    hipLaunchKernelGGL((mfma_setup_kernel<BF, DM, X3>), dim3(uint32_t(D)), dim3(kSetupThreads), 0,
+                       stream, lam, R, h0, int(d), static_cast<bf16x8*>(workspace),
+                       reinterpret_cast<float4*>(static_cast<char*>(workspace) +
+                                                 frag_bytes(BF, !X3, D, d)));
+    return hipGetLastError();
 }
 
 template <bool BF>
 hipError_t launch_setup(const float2* lam, const float2* R, const float* h0, int64_t D, int64_t d,
-                        void* workspace, hipStream_t stream)
+                        bool two_terms, void* workspace, hipStream_t stream)
 {
-    bf16x8* frag = static_cast<bf16x8*>(workspace);
-    float4* lamc = reinterpret_cast<float4*>(static_cast<char*>(workspace) + frag_bytes(BF, D, d));
-    const dim3 grid{uint32_t(D)}, block{kSetupThreads};
-#define LH_SETUP(K)                                                                              \
-    case K:                                                                                      \
-        hipLaunchKernelGGL((mfma_setup_kernel<BF, K>), grid, block, 0, stream, lam, R, h0, int(d), \
-                           frag, lamc);                                                          \
-        break;
+    // tables of float32 u and y serve either kernel
     switch (modes16(d)) {
-        LH_SETUP(1)
-        LH_SETUP(2)
-        LH_SETUP(3)
-        LH_SETUP(4)
+        case 1:
+            if (BF && two_terms)
+                return launch_setup_tiled<BF, 1, !BF>(lam, R, h0, D, d, workspace, stream);
+            return launch_setup_tiled<BF, 1, true>(lam, R, h0, D, d, workspace, stream);
+        case 2:
+            if (BF && two_terms)
+                return launch_setup_tiled<BF, 2, !BF>(lam, R, h0, D, d, workspace, stream);
+            return launch_setup_tiled<BF, 2, true>(lam, R, h0, D, d, workspace, stream);
+        case 3: return launch_setup_tiled<BF, 3, true>(lam, R, h0, D, d, workspace, stream);
+        case 4: return launch_setup_tiled<BF, 4, true>(lam, R, h0, D, d, workspace, stream);
         default: return hipErrorInvalidValue;
     }
-#undef LH_SETUP
-    return hipGetLastError();
 }
 
-static_assert(MfmaTiling<true, 1>::kFrags == 7 && MfmaTiling<true, 4>::kFrags == 25 &&
-                  MfmaTiling<false, 1>::kFrags == 9 && MfmaTiling<false, 4>::kFrags == 30,
+static_assert(MfmaTiling<true, 1, false>::kFrags == 7 && MfmaTiling<true, 2, false>::kFrags == 13 &&
+                  MfmaTiling<true, 1, true>::kFrags == 9 && MfmaTiling<true, 4, true>::kFrags == 30 &&
+                  MfmaTiling<false, 1, true>::kFrags == 9 && MfmaTiling<false, 4, false>::kFrags == 30,
               "frag_bytes counts these fragments");
 
 // Time of a pass in tiles of the busiest CU: its workgroups run one at a time,
@@ -279,9 +288,9 @@ size_t mfma_workspace_bytes(int64_t D, int64_t d)
     return (frag + 255) / 256 * 256 + size_t(D) * d * sizeof(float2);
 }
 
-size_t mfma_table_bytes(bool bf16_io, int64_t D, int64_t d)
+size_t mfma_table_bytes(bool bf16_io, bool two_terms, int64_t D, int64_t d)
 {
-    return frag_bytes(bf16_io, D, d) + size_t(D) * 16 * modes16(d) * sizeof(float4);
+    return frag_bytes(bf16_io, two_terms, D, d) + size_t(D) * 16 * modes16(d) * sizeof(float4);
 }
 
 // Segment slots of the segmented plan: the fewest segments (a power of two,
@@ -327,12 +336,13 @@ MfmaCut mfma_cut(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64
 }
 
 hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0, int64_t D,
-                             int64_t d, bool bf16_io, void* workspace, hipStream_t stream)
+                             int64_t d, bool bf16_io, bool two_terms, void* workspace,
+                             hipStream_t stream)
 {
     (void)hipGetLastError();
     if (D > 0x7fffffff) return hipErrorInvalidConfiguration;
-    return bf16_io ? launch_setup<true>(lam, R, h0, D, d, workspace, stream)
-                   : launch_setup<false>(lam, R, h0, D, d, workspace, stream);
+    return bf16_io ? launch_setup<true>(lam, R, h0, D, d, two_terms, workspace, stream)
+                   : launch_setup<false>(lam, R, h0, D, d, two_terms, workspace, stream);
 }
 
 hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool bf16_io,
@@ -350,7 +360,7 @@ hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool
     a.y = y;
     a.state = state;
     a.frag = workspace;
-    a.lamc = static_cast<const char*>(workspace) + frag_bytes(bf16_io, D, d);
+    a.lamc = static_cast<const char*>(workspace) + frag_bytes(bf16_io, cut.two_terms, D, d);
     a.xs = xs;
     a.T = T;
     a.seg_len = cut.seg_len;

@@ -91,11 +91,12 @@ __device__ __forceinline__ void split8(const f32x4 a, const f32x4 b, bf16x8 (&ou
 }
 
 // S: time chunks per row among the 16 columns.  OUT = false is the state pass
-// of the segmented plan (end states only).
-template <typename IO, int DM, int S, bool OUT, bool X2>
+// of the segmented plan (end states only).  X3: three terms of every float32 operand
+// and entry state, else two where the outputs allow it.
+template <typename IO, int DM, int S, bool OUT, bool X3>
 __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
 {
-    using Cf = MfmaTiling<sizeof(IO) == 2, DM>;
+    using Cf = MfmaTiling<sizeof(IO) == 2, DM, X3>;
     constexpr bool BF = sizeof(IO) == 2;
     constexpr int ES = int(sizeof(IO));
     constexpr int CPW = Cf::kCpw, CW = Cf::kCw, NF = Cf::kFrags;
@@ -106,8 +107,8 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     constexpr int NITEM = R * (S * kC / 4) * PQ;  // (row, four steps, piece) items, at most one per thread
     static_assert(NITEM <= kThreads, "one item per thread");
     constexpr int NTU = BF ? 1 : 3;            // bfloat16 terms of u
-    constexpr int NTW = BF ? 2 : 3;            // of W
-    constexpr int NTX = BF || X2 ? 2 : 3;      // of the entry states
+    constexpr int NTW = BF && !X3 ? 2 : 3;     // of W
+    constexpr int NTX = X3 ? 3 : 2;            // of the entry states
     constexpr int LPC = 16 * DM;               // modes per channel = scan lanes
     constexpr int RHX = 64 / (CPW * LPC) > 0 ? 64 / (CPW * LPC) : 1;
     constexpr int RH = RHX < R ? RHX : R;      // row groups of the scan
@@ -284,15 +285,20 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
         }
         return o;
     };
-    // Products with U, one instruction each.  T: with bfloat16 u [a1 | a2] u, with
-    // float32 u (a1 + a2) u1, (a1 + a2) u2, a1 u3 + a3 u1.  P: with bfloat16 u
-    // [a1 | a2] u and [a3 | 0] u, with float32 u as T.
-    constexpr int NPT = BF ? 1 : 3, NPP = BF ? 2 : 3;
+    // Products with U, one instruction each, with three terms the smallest first, so that the sum is
+    // rounded at its full size as few times as possible.  With float32 u
+    // a1 u3 + a3 u1, (a1 + a2) u2, (a1 + a2) u1; with bfloat16 u [a3 | 0] u (of T only
+    // with three terms) and [a1 | a2] u.
+    constexpr int NPP = BF ? 2 : 3, NPT = BF && !X3 ? 1 : NPP;
+    auto mul_u = [&](f32x4 acc, int k, int frag, const Operands& o, int i, int n) {
+        const int j = X3 ? n - 1 - i : i;  // 0: the largest
+        return mfma(A[k][frag + (BF ? j : j < 2 ? 0 : 1)], o.u[BF ? 0 : j], acc);
+    };
     auto mul_t = [&](f32x4 acc, int k, const Operands& o, int i) {
-        return mfma(A[k][i < 2 ? 0 : 1], o.u[BF ? 0 : i], acc);
+        return mul_u(acc, k, 0, o, i, NPT);
     };
     auto mul_p = [&](f32x4 acc, int k, int f, const Operands& o, int i) {
-        return mfma(A[k][Cf::kP + 2 * f + (BF ? i : i < 2 ? 0 : 1)], o.u[BF ? 0 : i], acc);
+        return mul_u(acc, k, Cf::kP + 2 * f, o, i, NPP);
     };
 
     // ---- S = 1: the states of column n in the accumulator layout, X[k][f] holding
@@ -354,11 +360,11 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     // one before it.
     auto products = [&](int k, const Operands& o, f32x4 (&x)[2 * DM], auto step) {
         constexpr bool STEP = decltype(step)::value;
-        // (W term, X term) pairs: i + j < 2 with bfloat16 u and y, i + j < 3 with
-        // float32, there (1, 1) and (0, 2) only with three terms of X
-        constexpr int NW = BF ? 3 : NTX == 2 ? 4 : 6;
-        constexpr int kTa[6] = {0, 0, 1, 2, 1, 0};
-        constexpr int kTb[6] = {0, 1, 0, 0, 1, 2};
+        // (W term, X term) pairs: all with i + j < 3, the smallest first; in the two-term
+        // kernels i + j < 2 with bfloat16 u and y, else without (1, 1) and (0, 2)
+        constexpr int NW = X3 ? 6 : BF ? 3 : 4;
+        constexpr int kTa[6] = {0, X3 ? 2 : 0, 1, X3 ? 1 : 2, 0, 0};
+        constexpr int kTb[6] = {X3 ? 2 : 0, X3 ? 0 : 1, X3 ? 1 : 0, 0, 1, 0};
         constexpr int NY = DM == 1 ? 1 : 2;  // chains of Y
         f32x4 y[NY] = {};
 #pragma unroll
@@ -373,8 +379,8 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
             for (int i = 0; i < ROUNDS; ++i) {
                 if (q == 0 && i < NPT) y[0] = mul_t(y[0], k, o, i);
                 if (i < NW)
-                    y[(q + 1) % NY] =
-                        mfma(A[k][Cf::kW + q * NTW + kTa[i]], xb[kTb[i]], y[(q + 1) % NY]);
+                    y[(q + 1) % NY] = mfma(A[k][Cf::kW + q * NTW + kTa[i]],
+                                           xb[kTb[i]], y[(q + 1) % NY]);
                 if (STEP && i < NPP)
 #pragma unroll
                     for (int f = 2 * q; f < 2 * q + 2; ++f) x[f] = mul_p(x[f], k, f, o, i);
@@ -611,10 +617,10 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     }
 }
 
-template <typename IO, int DM, int S, bool OUT, bool X2>
+template <typename IO, int DM, int S, bool OUT, bool X3>
 hipError_t launch_tiled(MfmaArgs a, hipStream_t stream)
 {
-    using Cf = MfmaTiling<sizeof(IO) == 2, DM>;
+    using Cf = MfmaTiling<sizeof(IO) == 2, DM, X3>;
     constexpr int PB = Cf::kCw * int(sizeof(IO)), CPL = 128 / PB > 1 ? 128 / PB : 1, R = kN / S;
     const int64_t rows = int64_t(a.B) * (S == kN ? (OUT ? a.nseg : a.nseg - 1) : 1);
     const int64_t ncg = (int64_t(a.D) + Cf::kCw - 1) / Cf::kCw, nrg = (rows + R - 1) / R;
@@ -623,19 +629,20 @@ hipError_t launch_tiled(MfmaArgs a, hipStream_t stream)
     a.ncg = int(ncg);
     a.nrg = int(nrg);
     a.per_xcd = int(per_xcd);
-    hipLaunchKernelGGL((mfma_prefill_kernel<IO, DM, S, OUT, X2>), dim3(uint32_t(8 * per_xcd)),
+    hipLaunchKernelGGL((mfma_prefill_kernel<IO, DM, S, OUT, X3>), dim3(uint32_t(8 * per_xcd)),
                        dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 
-template <typename IO, int DM, bool X2>
-hipError_t launch_s(int s, const MfmaArgs& a, hipStream_t stream)
+template <typename IO, int DM, bool X3>
+hipError_t launch_s(int s, bool outputs, const MfmaArgs& a, hipStream_t stream)
 {
+    if (!outputs) return launch_tiled<IO, DM, 16, false, X3>(a, stream);
     switch (s) {
-        case 1: return launch_tiled<IO, DM, 1, true, X2>(a, stream);
-        case 2: return launch_tiled<IO, DM, 2, true, X2>(a, stream);
-        case 4: return launch_tiled<IO, DM, 4, true, X2>(a, stream);
-        case 16: return launch_tiled<IO, DM, 16, true, X2>(a, stream);
+        case 1: return launch_tiled<IO, DM, 1, true, X3>(a, stream);
+        case 2: return launch_tiled<IO, DM, 2, true, X3>(a, stream);
+        case 4: return launch_tiled<IO, DM, 4, true, X3>(a, stream);
+        case 16: return launch_tiled<IO, DM, 16, true, X3>(a, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -643,10 +650,11 @@ hipError_t launch_s(int s, const MfmaArgs& a, hipStream_t stream)
 template <typename IO, int DM>
 hipError_t launch_dm(int s, bool outputs, const MfmaArgs& a, hipStream_t stream)
 {
-    if (!outputs) return launch_tiled<IO, DM, 16, false, false>(a, stream);
-    if constexpr (sizeof(IO) == 4 && DM != 3)
-        if (a.two_terms && a.d == 16 * DM) return launch_s<IO, DM, true>(s, a, stream);
-    return launch_s<IO, DM, false>(s, a, stream);
+    if (!a.two_terms) return launch_s<IO, DM, true>(s, outputs, a, stream);
+    // the orders of the explicit plans
+    if constexpr (DM <= 2 || (DM == 4 && sizeof(IO) == 4))
+        if (a.d == 16 * DM) return launch_s<IO, DM, false>(s, outputs, a, stream);
+    return hipErrorInvalidValue;
 }
 
 template <typename IO>

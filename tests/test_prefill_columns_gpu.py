@@ -143,27 +143,27 @@ def test_scratch_limits():
     assert torch.equal(held[0], scan[0]) and torch.equal(held[1], scan[1])
 
 
-@pytest.mark.parametrize("case", [(5, 520, 16, 4003), (3, 512, 32, 2001), (3, 520, 64, 1003)],
-                         ids=lambda c: "B%d_D%d_d%d_T%d" % c)
-def test_error_is_the_scans(case):
-    """Orders 16, 32 and 64 at prompts that no named plan takes: slow poles, whose
-    large entry states show how many terms of them are kept.  Three terms leave a
-    relative error of 2^-24 per product, as float32 does, so the error against
-    float64 is at most half as large again as the scan's, or 1e-6."""
+ERROR_CASES = [(5, 520, 16, 4003), (3, 512, 32, 2001), (3, 520, 64, 1003)]
+
+
+def _errors(case, io):
+    """Outputs of the automatic call, of the VALU scan in one pass and in float64, for
+    slow poles, whose large entry states show how many terms of them are kept."""
     import torch
 
     import paper_2310_18780_amd as lh
 
     B, D, d, T = case
-    w = workloads.Workload("case", B, D, d, T, 0, "f32", 0.99, 0.9999, 0.1 * np.pi, 1.0 / d, 3)
+    w = workloads.Workload("case", B, D, d, T, 0, io, 0.99, 0.9999, 0.1 * np.pi, 1.0 / d, 3)
     lam, R, h0 = workloads.make_params(w)
     t = to_device(lam, R, h0, np.zeros((1, 1, D), np.float32), np.zeros((1, 0, D), np.float32), "f32")
     g = torch.Generator(device="cuda").manual_seed(3)
-    u = torch.randn((B, T, D), generator=g, device="cuda")
-    print(f"[error] {case}", flush=True)
+    u = torch.randn((B, T, D), generator=g, device="cuda").to(
+        torch.bfloat16 if io == "bf16" else torch.float32)
+    print(f"[error] {case} {io}", flush=True)
     auto = _run(lambda x, y: lh.prefill(t["lam"], t["R"], t["h0"], u, x, y), u, d)
     scan = _run(lambda x, y: lh.prefill_with_plan(t["lam"], t["R"], t["h0"], u, x, y, T), u, d)
-    assert lh.prefill_path(B, D, d, T)[0] == "mfma"
+    assert lh.prefill_path(B, D, d, T, io=io)[0] == "mfma"
     k = torch.arange(T - 1, device="cuda", dtype=torch.float64)
     h = torch.empty((T, D), dtype=torch.float64, device="cuda")
     h[0] = t["h0"].double()
@@ -173,6 +173,29 @@ def test_error_is_the_scans(case):
         h[1:] += (t["R"][:, n].to(torch.complex128) * p).real
     N = 1 << (2 * T - 1).bit_length()
     y = torch.fft.irfft(torch.fft.rfft(u.double(), N, dim=1) * torch.fft.rfft(h, N, dim=0), N, dim=1)[:, :T]
-    err = [float((r[0].double() - y).norm() / y.norm()) for r in (auto, scan)]
+    return auto[0].double(), scan[0].double(), y
+
+
+@pytest.mark.parametrize("case", ERROR_CASES, ids=lambda c: "B%d_D%d_d%d_T%d" % c)
+def test_error_is_the_scans(case):
+    """Orders 16, 32 and 64 at prompts that no named plan takes.  Three terms leave a
+    relative error of 2^-24 per product, as float32 does, so the error against
+    float64 is at most half as large again as the scan's, or 1e-6."""
+    auto, scan, y = _errors(case, "f32")
+    err = [float((a - y).norm() / y.norm()) for a in (auto, scan)]
     print(f"[error] {err}", flush=True)
     assert err[0] <= max(1e-6, 1.5 * err[1]), err
+
+
+@pytest.mark.parametrize("case", ERROR_CASES, ids=lambda c: "B%d_D%d_d%d_T%d" % c)
+def test_error_of_cancelling_bfloat16_outputs_is_the_scans(case):
+    """The same with bfloat16 u and y, at the outputs below 2e-3 of their row's size:
+    their rounding (2^-9 of themselves, 1.9e-6 of the row over these) hides an error
+    of float32 arithmetic, while two bfloat16 terms (2^-17 of the row's size, 4e-6
+    over these) more than double what is left."""
+    auto, scan, y = _errors(case, "bf16")
+    rms = y.square().mean(dim=1, keepdim=True).sqrt()
+    small = y.abs() < 2e-3 * rms
+    err = [float((((a - y) / rms)[small]).square().mean().sqrt()) for a in (auto, scan)]
+    print(f"[error] {err}", flush=True)
+    assert err[0] <= 1.1 * err[1], err
