@@ -149,8 +149,8 @@ def mfma64_flops(w):
     products, 16384 flops each; float32 operands in three bfloat16 terms): per
     channel, 16 columns (rows, or chunks of a row) of a 16-step chunk, 24
     products for the chunk's end state (8 row tiles of P U, K holding two terms
-    of 16 steps), 3 for the outputs from the chunk's inputs (T U) and 16 for
-    those from its entry state (W X: 4 K tiles x 4 term products)."""
+    of 16 steps), 3 for the outputs from the chunk's inputs (T U) and 20 for
+    those from its entry state (W X: 4 K tiles x 5 term products)."""
     return 16384 * w.D * -(-w.B // 16) * 43 * -(-w.T // 16)
 
 
@@ -894,8 +894,8 @@ def main():
     # The matrix-core plans at d = 16 and 32 execute their split-term
     # contractions below the bfloat16 MFMA ridge (at most 240 flops per byte of
     # u and y, d = 32 with bfloat16 u and y, against 2500 / 8 = 312), so their
-    # roofline is HBM; at d = 64 the 43 products per channel, 16 columns and 16
-    # steps come to 344 flops per byte, above the ridge, so its roofline is the
+    # roofline is HBM; at d = 64 the 47 products per channel, 16 columns and 16
+    # steps come to 376 flops per byte, above the ridge, so its roofline is the
     # bfloat16 MFMA peak; the VALU scan is held against the VALU peak.
     plan = lh.prefill_plan(w.B, w.D, w.d, w.T, io=w.io)
     path, columns, segments = lh.prefill_path(w.B, w.D, w.d, w.T, io=w.io)

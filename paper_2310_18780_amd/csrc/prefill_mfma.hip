@@ -20,11 +20,12 @@
 // so that y_t = Re(R x_t) + h0 u_t at every step and the last entry state is x_T.
 //
 // Columns.  The 16 columns are 16/S batch rows times S consecutive chunks of
-// each: the end states S are exchanged through LDS (within the wave that owns
-// the channel, no barrier), one lane per (channel, mode) walks the columns of a
-// row in order and leaves the entry states in their place.  The prompt of one
-// row is thus a single pass at any batch size: S = 2 for many rows, S = 16 (256
-// steps of one row at a time) for few.  Only where (channel group, row) pairs
+// each.  S = 1, for many rows: a column is a row, its states stay in registers.
+// S = 2, 4 or 16 (256 steps of one row at a time), for few: the end states are
+// exchanged through LDS (within the wave that owns the channel, no barrier), one
+// lane per (channel, mode) walks the columns of a row in order and leaves the entry
+// states in their place.  The prompt of one row is thus a single pass at any batch
+// size.  Only where (channel group, row) pairs
 // are too few to occupy the GPU is the prompt cut into segments as well
 // (segmented plan): a pass for the segments' end states from zero, a carry,
 // and the pass from the carried entry states.
@@ -33,13 +34,21 @@
 // operand is split into bfloat16 terms a = a1 + a2 (+ a3), each the nearest
 // bfloat16 of what the previous terms leave.  U has K = 16, half of the
 // instruction's K, so two products share one instruction: [a1 | a2] times
-// [u; u] is (a1 + a2) u.  With float32 u and y all operands have three terms
-// and a product takes the six pairs with i + j <= 2 (an error of a few
-// float32 ulps of |a b|).  Bfloat16 u is exact in one term; its outputs are
-// rounded to bfloat16, so T, W and the entry states as operand of W take two
-// terms (relative error near 2^-17, invisible after the rounding) while P keeps
-// three: the end states, and through the scan x_T, are formed at float32
-// precision.  The matrices and lambda^C come from float64 powers, rounded
+// [u; u] is (a1 + a2) u.  Two kernels:
+//   three terms of every operand, products of the six pairs with i + j <= 2 (an
+//   error of a few float32 ulps of |a b|): every size that the VALU scan would take
+//   otherwise, and unaligned u or y;
+//   two terms where the outputs allow it: the plans that callers name, or that the
+//   automatic call takes at their sizes.  With float32 u and y the entry states
+//   have two terms (error of the outputs 2e-6 of their norm at radii U[0.9, 0.9999],
+//   2.4e-6 at U[0.999, 0.99999]; 3.1e-6 and 3.6e-6 without the product of the second
+//   terms), all else three.  With bfloat16 u (exact in one term) and y (rounded)
+//   T, W and the entry states have two (2^-17 of a row's size, lost in the rounding
+//   but of outputs that cancel), P three: the end states, and through the scan
+//   x_T, are formed at float32 precision in either kernel.
+// Small products come before large ones: the sums are then rounded at their full
+// size only once or twice (x_T at radii U[0, 0.5]: 6.5e-8 against 8.2e-8).
+// The matrices and lambda^C come from float64 powers, rounded
 // once; lambda^C keeps the error of its rounding beside it (it would repeat every
 // 16 steps with the same sign).  d is padded to a multiple of 16 with
 // modes of zero operands.

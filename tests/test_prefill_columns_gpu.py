@@ -199,3 +199,29 @@ def test_error_of_cancelling_bfloat16_outputs_is_the_scans(case):
     err = [float((((a - y) / rms)[small]).square().mean().sqrt()) for a in (auto, scan)]
     print(f"[error] {err}", flush=True)
     assert err[0] <= 1.1 * err[1], err
+
+
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_second_terms_of_a_named_plan(d):
+    """The float32 plans that keep two terms of the entry states: state and residue
+    1 + 2^-8 - 2^-14 each, both just two terms, so that only the product of the
+    second ones (1.5e-5 here, the largest there is) could be missing; third terms
+    and roundings stay below 2^-21."""
+    import torch
+
+    import paper_2310_18780_amd as lh
+
+    B, D, T = 2, 8, 512
+    v = 1 + 2.0 ** -8 - 2.0 ** -14
+    lam = torch.zeros((D, d), dtype=torch.complex64, device="cuda")
+    R, h0 = torch.zeros_like(lam), torch.zeros(D, device="cuda")
+    lam[:, d // 2] = 1.0
+    R[:, d // 2] = v
+    u = torch.zeros((B, T, D), device="cuda")
+    u[:, 0] = v
+    for plan in (lh.PLAN_MFMA, lh.PLAN_MFMA_SEG):
+        y, x = _run(lambda x, y: lh.prefill_with_plan(lam, R, h0, u, x, y, plan), u, d)
+        err = float((y[:, 1:].double() - v * v).abs().max())
+        print(f"[second terms] d={d} plan={plan} {err}", flush=True)
+        assert err <= 2.0 ** -21
+        assert bool((x[:, :, d // 2] == v).all())
