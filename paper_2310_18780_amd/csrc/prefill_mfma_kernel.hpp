@@ -70,6 +70,13 @@ __device__ __forceinline__ void wave_order()
     asm volatile("" ::: "memory");
 }
 
+__device__ __forceinline__ float2 cmul(float2 a, float2 b)
+{
+    return make_float2(fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x));
+}
+
+__device__ __forceinline__ float2 add(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+
 // B operand of W X_in: 8 state components as NT bfloat16 terms
 template <int NT>
 __device__ __forceinline__ void split8(const f32x4 a, const f32x4 b, bf16x8 (&out)[NT])
@@ -172,10 +179,15 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     const bool scan_on = srh < RH;
     const int sc = min(c0 + w * CPW + sk, D - 1);
     const float4 lp = static_cast<const float4*>(p.lamc)[int64_t(sc) * LPC + sm];
-    // tiles between corrections of lambda^C's rounding (lp.z, lp.w relative to it)
-    // and what it amounts to by then
-    constexpr int kCorrect = S >= 4 ? 1 : 4;
-    constexpr float kSteps = kCorrect * S;
+    // The rounding of lambda^C (lp.z, lp.w relative to it) is put right every kSteps
+    // chunks, for the whole state as if all of it had taken kSteps products since: what
+    // entered later is over-corrected, by at most kSteps roundings of lambda^C (2.4e-7
+    // relative; with poles so fast that little older remains it shows, and every 16
+    // chunks came to 1e-6).
+    constexpr int kSteps = 4;
+    constexpr int kCorrect = S >= kSteps ? 1 : kSteps / S;  // tiles between corrections
+    const float2 ec = cmul(make_float2(kSteps * lp.z, kSteps * lp.w), make_float2(lp.x, lp.y));
+    const float2 ec2 = cmul(ec, make_float2(lp.x, lp.y));
     float xr[RL], xi[RL];
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
@@ -440,7 +452,7 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
                     for (int f = 0; f < 2 * DM; ++f) {
                         const f32x4 e =
                             *reinterpret_cast<const f32x4*>(corr + 2 * (k * LPC + 8 * f + 2 * g));
-                        X[k][f] += kSteps * mul_lambda(e, X[k][f]);
+                        X[k][f] += float(kSteps) * mul_lambda(e, X[k][f]);
                     }
             }
         f32x4 Y[CPW];
@@ -507,22 +519,29 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
                 xi[r] = fmaf(lp.x, xi[r], fmaf(lp.y, xr[r], z.y));
                 xr[r] = nr;
             };
-            if (!decltype(first)::value && tile % kCorrect == 0)
-#pragma unroll
-                for (int r = 0; r < RL; ++r) {
-                    const float er = kSteps * lp.z, ei = kSteps * lp.w;
-                    const float nr = fmaf(er, xr[r], fmaf(-ei, xi[r], xr[r]));
-                    xi[r] = fmaf(er, xi[r], fmaf(ei, xr[r], xi[r]));
-                    xr[r] = nr;
-                }
+            auto due = [&](int s) {
+                return s % kSteps == 0 && (s > 0 || (!decltype(first)::value && tile % kCorrect == 0));
+            };
             if constexpr (decltype(whole)::value) {
+                // the correction of the state before one column joins the sum of the next
+                // one, as its smallest term (added to the state by itself it would cost a
+                // rounding of it) and out of the chain of the walk, which a long walk waits
+                // for; the short one has no registers for it
+                constexpr bool kLate = S >= kSteps;
+                float2 late[kLate ? RL : 1];
 #pragma unroll
                 for (int s = 0; s < S; ++s)
 #pragma unroll
                     for (int r = 0; r < RL; ++r) {
                         float2* e = xp + (r * S + s) * (XST / 2);
-                        const float2 z = *e;
+                        float2 z = *e;
                         if constexpr (OUT) *e = make_float2(xr[r], xi[r]);
+                        if constexpr (kLate) {
+                            if (s > 0 && due(s - 1)) z = add(z, late[r]);
+                            if (due(s)) late[r] = cmul(ec2, make_float2(xr[r], xi[r]));
+                        } else if (due(s)) {
+                            z = add(z, cmul(ec, make_float2(xr[r], xi[r])));
+                        }
                         advance(r, z);
                     }
             } else {  // whole chunks, then the remaining steps one by one
@@ -532,8 +551,9 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
 #pragma unroll
                     for (int r = 0; r < RL; ++r) {
                         float2* e = xp + (r * S + s) * (XST / 2);
-                        const float2 z = *e;
+                        float2 z = *e;
                         *e = make_float2(xr[r], xi[r]);
+                        if (due(s)) z = add(z, cmul(ec, make_float2(xr[r], xi[r])));
                         advance(r, z);
                     }
 #pragma unroll

@@ -225,3 +225,37 @@ def test_second_terms_of_a_named_plan(d):
         print(f"[second terms] d={d} plan={plan} {err}", flush=True)
         assert err <= 2.0 ** -21
         assert bool((x[:, :, d // 2] == v).all())
+
+
+@pytest.mark.parametrize("d,plan", [(12, 0), (16, -1)])
+def test_correction_of_a_young_state(d, plan):
+    """The rounding of lambda^16 is put right for a whole state at once, also for what
+    has not been multiplied by it since: by at most four roundings (2^-24 each),
+    whichever chunk the state entered in.  A pole whose lambda^16 is rounded by almost
+    2^-24, one input at the last step of a chunk, the output of the next step."""
+    import torch
+
+    import paper_2310_18780_amd as lh
+
+    lam32 = np.arange(np.float32(0.75), np.float32(0.86), np.float32(2.0 ** -20), dtype=np.float32)
+    p = lam32.astype(np.float64) ** 16
+    e = np.abs(p.astype(np.float32) / p - 1)
+    assert e.max() > 0.9 * 2.0 ** -24
+    B, D, T = 16, 512, 512
+    assert lh.prefill_path(B, D, d, T, plan=plan)[:2] == ("mfma", 16)
+    lam = torch.zeros((D, d), dtype=torch.complex64, device="cuda")
+    R, h0 = torch.zeros_like(lam), torch.zeros(D, device="cuda")
+    lam[:, 3] = float(lam32[e.argmax()])
+    R[:, 3] = 1.0
+    u = torch.zeros((B, T, D), device="cuda")
+    for b in range(B):  # a row for each chunk of the second 256 steps
+        u[b, 255 + 16 * b] = 1.0
+    y, _ = _run(lambda x, y: lh.prefill_with_plan(lam, R, h0, u, x, y, plan), u, d)
+    # a chunk later with that product's rounding and the state's own (the named plan's
+    # two terms of lambda^16, to 2^-17, would hide it there)
+    for chunk in (0, 1) if plan == 0 else (0,):
+        want = p[e.argmax()] ** chunk
+        err = [float((y[b, 256 + 16 * (b + chunk)].double() - want).abs().max()) / want / 2.0 ** -24
+               for b in range(B - chunk)]
+        print(f"[young state] d={d} plan={plan} {err}", flush=True)
+        assert max(err) <= 4 + 1 + 2 * chunk  # and the rounding of the output
