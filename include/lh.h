@@ -121,9 +121,12 @@ size_t lh_prefill_workspace_bytes(int64_t B, int64_t D, int64_t d, int64_t T);
  * must be split in time to fill it, else the general chunked scan, which runs
  * on the matrix cores too where its sizes allow and that is faster (see
  * lh_prefill_with_plan for what each computes and needs).  Every plan gives
- * the same results up to float32 rounding.  On the matrix cores an input that
- * is not finite makes the outputs of its (row, channel) from the start of its
- * 16-step chunk on not finite.
+ * the same results within the accuracy of its arithmetic: float32 rounding, but
+ * for plans named LH_PLAN_MFMA and LH_PLAN_MFMA_SEG with 16-byte aligned u and y
+ * the two-term operands described at lh_prefill_with_plan.  An input that is not
+ * finite affects its (row, channel) from its own step on; in those two plans, with
+ * such u and y, from the start of its 16-step chunk on (the outputs before it in
+ * the chunk are lost too).
  * T == 0 zeroes the state and leaves y untouched.  y must not overlap u,
  * state, lambda, R, h0 or workspace; state must not overlap any input.
  */
@@ -216,7 +219,8 @@ size_t lh_prefill_with_plan_workspace_bytes(int64_t B, int64_t D, int64_t d, int
  *            16 columns of a product are batch rows, or fewer rows and several
  *            chunks of each; with
  *            the float32 operands split into bfloat16 terms: three with
- *            float32 u/y, two for the outputs and three for the state with
+ *            float32 u/y, but two of X_in (error of the outputs near 2e-6 of
+ *            their norm); two for the outputs and three for the state with
  *            bfloat16 u/y; d = 16 or 32 require D % 8 == 0, d = 64 requires
  *            float32 u/y and D % 4 == 0; always T >= 1 and 16-byte aligned u and
  *            y, else LH_ERR_INVALID_ARG).  The automatic plan, which takes any
@@ -242,8 +246,10 @@ size_t lh_prefill_with_plan_workspace_bytes(int64_t B, int64_t D, int64_t d, int
  *            is supported but not chosen and T splits this way (at d = 64
  *            only when B * T > 1024).
  * Elsewhere an automatic call runs the general chunked scan: the matrix-core
- * pass above where d <= 64 and a fitted estimate of both times favours it, else,
- * or with a workspace that holds only the VALU scan's states, the VALU scan.
+ * pass above, every operand in three terms, where d <= 64 and a fitted estimate
+ * of both times favours it, else, or with a workspace that does not hold its
+ * tables (but the VALU scan's states, if it has any), the VALU scan.  A named
+ * automatic plan whose u or y is not 16-byte aligned takes three terms too.
  * workspace: at least lh_prefill_with_plan_workspace_bytes(B,D,d,T,plan)
  * bytes.  A plan request the sizes do not support returns LH_ERR_INVALID_ARG.
  */

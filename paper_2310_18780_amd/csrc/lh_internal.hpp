@@ -93,10 +93,10 @@ hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0
 // One pass: outputs = false writes each segment's end state from zero into slot
 // k < nseg - 1 of xs [B, nseg, D, d]; outputs = true runs every segment from its
 // entry state in xs (the whole prompt from zero when nseg = 1), writes y and x_T.
-hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool bf16_io,
-                            int64_t B, int64_t D, int64_t d, int64_t T, const MfmaCut& cut,
-                            float2* xs, float2* state, void* y, const void* workspace,
-                            hipStream_t stream);
+hipError_t launch_mfma_pass(bool outputs, const float2* lam, const float2* R, const float* h0,
+                            const void* u, bool bf16_io, int64_t B, int64_t D, int64_t d,
+                            int64_t T, const MfmaCut& cut, float2* xs, float2* state, void* y,
+                            const void* workspace, hipStream_t stream);
 
 hipError_t launch_step(const float2* lam, const float2* R, const float* h0, float2* state,
                        const void* u_t, void* y_t, bool bf16_io, int64_t B, int64_t D,

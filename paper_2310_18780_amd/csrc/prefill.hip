@@ -493,14 +493,14 @@ hipError_t launch_prefill(const float2* lam, const float2* R, const float* h0, c
             hipLaunchKernelGGL(pow_kernel, g_pow, dim3(kBlock), 0, stream, lam, lamC, D * d,
                                cut.seg_len);
             if ((e = hipGetLastError()) != hipSuccess) return e;
-            if ((e = launch_mfma_pass(false, lam, u, bf16_io, B, D, d, T, cut, xs, state, y, mws,
-                                      stream)) != hipSuccess)
+            if ((e = launch_mfma_pass(false, lam, R, h0, u, bf16_io, B, D, d, T, cut, xs, state, y,
+                                      mws, stream)) != hipSuccess)
                 return e;
             hipLaunchKernelGGL(carry_kernel, g_state, dim3(kBlock), 0, stream, lamC, xs, B, D * d,
                                int64_t(cut.nseg));
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        return launch_mfma_pass(true, lam, u, bf16_io, B, D, d, T, cut, xs, state, y, mws, stream);
+        return launch_mfma_pass(true, lam, R, h0, u, bf16_io, B, D, d, T, cut, xs, state, y, mws, stream);
     }
     float2* lamC = nullptr;
     float2* xs = nullptr;

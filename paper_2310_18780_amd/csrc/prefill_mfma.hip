@@ -354,10 +354,10 @@ hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0
                    : launch_setup<false>(lam, R, h0, D, d, two_terms, workspace, stream);
 }
 
-hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool bf16_io,
-                            int64_t B, int64_t D, int64_t d, int64_t T, const MfmaCut& cut,
-                            float2* xs, float2* state, void* y, const void* workspace,
-                            hipStream_t stream)
+hipError_t launch_mfma_pass(bool outputs, const float2* lam, const float2* R, const float* h0,
+                            const void* u, bool bf16_io, int64_t B, int64_t D, int64_t d,
+                            int64_t T, const MfmaCut& cut, float2* xs, float2* state, void* y,
+                            const void* workspace, hipStream_t stream)
 {
     (void)hipGetLastError();
     if (cut.nseg > 1 && (cut.s != 16 || cut.seg_len % kTile != 0 ||
@@ -365,6 +365,8 @@ hipError_t launch_mfma_pass(bool outputs, const float2* lam, const void* u, bool
         return hipErrorInvalidValue;
     MfmaArgs a{};
     a.lam = lam;
+    a.R = R;
+    a.h0 = h0;
     a.u = u;
     a.y = y;
     a.state = state;

@@ -32,7 +32,8 @@ inline int mfma_channels(bool bf, int dm)
 }
 
 struct MfmaArgs {
-    const float2* lam;
+    const float2 *lam, *R;
+    const float* h0;
     const void* u;
     void* y;
     float2* state;

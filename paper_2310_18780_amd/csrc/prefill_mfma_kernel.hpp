@@ -133,6 +133,7 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     constexpr bool kLocal = S == 1;            // a column is a row: its states stay in registers
     __shared__ __attribute__((aligned(16))) float xbuf[kWaves][kLocal ? 4 * CPW * LPC : CPW * kN * XST];
     __shared__ __attribute__((aligned(16))) unsigned char ybuf[2][OUT ? kN * YCOL : 16];
+    __shared__ int lost_any;  // whether a state of the workgroup is not finite at its end
 
     // ---- workgroup -> (channel group, row group).  The CPL channel groups of a
     // 128-byte line of u and y form a line group; logical index (line group, row
@@ -162,6 +163,7 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     const int tid = threadIdx.x;
     const int w = tid / 64, lane = tid % 64;
     const int g = lane / 16, n = lane % 16;
+    if (X3 && tid == 0) lost_any = 0;
 
     bf16x8 A[CPW][NF];
 #pragma unroll
@@ -611,31 +613,102 @@ __global__ __launch_bounds__(kThreads) void mfma_prefill_kernel(MfmaArgs p)
     }
     if constexpr (OUT) write_y(ntile - 1, ybuf[(ntile - 1) & 1], true);
 
-    if constexpr (kLocal) {  // x_T
+    // ---- x_T (of the last segment), or the end state of the segment, and the (row,
+    // channel) pairs whose state is not finite: bit row * CPW + channel of the wave
+    uint64_t lost = 0;
+    if constexpr (kLocal) {
 #pragma unroll
         for (int k = 0; k < CPW; ++k) {
             const int c = c0 + w * CPW + k, row = row0 + n;
-            if (c >= D || row >= nrow) continue;
+            const bool on = c < D && row < nrow;
             float2* dst = p.state + (int64_t(row) * D + c) * d;
+            float z = 0.f;  // not zero after a value that is not finite
 #pragma unroll
             for (int f = 0; f < 2 * DM; ++f)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
-                    if (8 * f + 2 * g + h < d)
-                        dst[8 * f + 2 * g + h] = make_float2(X[k][f][2 * h], X[k][f][2 * h + 1]);
+                    if (on && 8 * f + 2 * g + h < d) {
+                        const float2 v = make_float2(X[k][f][2 * h], X[k][f][2 * h + 1]);
+                        dst[8 * f + 2 * g + h] = v;
+                        if constexpr (X3) z += 0.f * v.x + 0.f * v.y;
+                    }
+            if constexpr (X3) {
+                uint64_t bad = __ballot(z != 0.f);
+                bad = (bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xffff;
+                for (int r = 0; bad != 0 && r < R; ++r) lost |= (bad >> r & 1) << (r * CPW + k);
+            }
         }
-        return;
-    }
-    // ---- x_T (of the last segment), or the end state of the segment
-    if (scan_on && sm < d && w * CPW + sk < D) {
+    } else {
+        const bool on = scan_on && sm < d && w * CPW + sk < D;
 #pragma unroll
         for (int r = 0; r < RL; ++r) {
             const int row = row0 + srh * RL + r;
-            if (row >= nrow || (OUT && seg != sv - 1)) continue;
+            if constexpr (X3) {
+                const float z = 0.f * xr[r] + 0.f * xi[r];
+                const uint64_t bad = __ballot(on && row < nrow && z != 0.f);
+                for (int q = 0; bad != 0 && q < RH * CPW; ++q)
+                    if ((bad >> (q * LPC) & (~UINT64_C(0) >> (64 - LPC))) != 0)
+                        lost |= UINT64_C(1) << ((q / CPW * RL + r) * CPW + q % CPW);
+            }
+            if (!on || row >= nrow || (OUT && seg != sv - 1)) continue;
             float2* dst = OUT ? p.state + (int64_t(row / sv) * D + sc) * d
                               : p.xs + ((int64_t(row / sv) * p.nseg + seg) * D + sc) * d;
             dst[sm] = make_float2(xr[r], xi[r]);
         }
+    }
+
+    // ---- A product multiplies every input of its chunk, also by zeros, so an input
+    // that is not finite (or that its nearest bfloat16 is not) spoils outputs before
+    // it, and leaves a state that is not finite for good.  Such a row and channel is
+    // stepped again from its start, one lane per mode, once all stores of the
+    // workgroup to it are out (write_y spreads a row over the waves); the others keep
+    // their results.  Not in the two-term kernels, whose plans always lost the outputs
+    // of the chunk (and where this code costs 1-4% of the time, through the registers).
+    if constexpr (!X3) return;
+    if (lane == 0 && lost != 0) lost_any = 1;
+    lds_barrier();
+    if (lost_any == 0) return;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    constexpr int NG = 64 / LPC;  // pairs at a time
+    const int q = lane / LPC, m = lane % LPC;
+    for (int p0 = 0; p0 < R * CPW; p0 += NG) {
+        const uint64_t these = lost >> p0 & (~UINT64_C(0) >> (64 - NG));
+        if (these == 0) continue;
+        const bool on = q < NG && (these >> q & 1) != 0;
+        const int pair = on ? p0 + q : 0, row = min(row0 + pair / CPW, nrow - 1);
+        const int c = min(c0 + w * CPW + pair % CPW, D - 1);
+        const bool mode = on && m < d;
+        const float2 l1 = mode ? p.lam[int64_t(c) * d + m] : make_float2(0.f, 0.f);
+        const float2 r1 = mode ? p.R[int64_t(c) * d + m] : make_float2(0.f, 0.f);
+        const float h1 = p.h0[c];
+        const int64_t at = (int64_t(row / sv) * p.nseg + seg) * D + c;  // of segment states
+        float2 x = make_float2(0.f, 0.f);
+        if (OUT && S == kN && p.nseg > 1 && mode) x = p.xs[at * d + m];
+        const int64_t first = (int64_t(row / sv) * p.T + (S == kN ? seg * p.seg_len : 0)) * D + c;
+        for (int64_t t0 = 0; t0 < TL; t0 += LPC) {
+            const int cnt = int(min(int64_t(LPC), TL - t0));
+            const int64_t mine = first + (t0 + min(m, cnt - 1)) * D;
+            const float ub = io_load(static_cast<const IO*>(p.u) + mine);
+            float yb = 0.f;
+            for (int j = 0; j < cnt; ++j) {
+                const float uv = __shfl(ub, q * LPC + j, 64);
+                if constexpr (OUT) {
+                    float v = mode ? fmaf(r1.x, x.x, -r1.y * x.y) : 0.f;
+                    for (int o = 1; o < (LPC == 48 ? 64 : LPC); o *= 2) v += __shfl_xor(v, o, 64);
+                    if (m == j) yb = fmaf(h1, uv, v);
+                }
+                x = make_float2(fmaf(l1.x, x.x, fmaf(-l1.y, x.y, uv)), fmaf(l1.x, x.y, l1.y * x.x));
+            }
+            if (OUT && on && m < cnt) io_store(static_cast<IO*>(p.y) + mine, yb);
+        }
+        if (!mode) continue;
+        if constexpr (!OUT)
+            p.xs[at * d + m] = x;
+        else if (seg == sv - 1)
+            p.state[(int64_t(row / sv) * D + c) * d + m] = x;
     }
 }
 

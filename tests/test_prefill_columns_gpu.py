@@ -259,3 +259,62 @@ def test_correction_of_a_young_state(d, plan):
                for b in range(B - chunk)]
         print(f"[young state] d={d} plan={plan} {err}", flush=True)
         assert max(err) <= 4 + 1 + 2 * chunk  # and the rounding of the output
+
+
+NOT_FINITE = [
+    (33, 1100, 30, 95, "f32"), (17, 1203, 45, 66, "f32"), (9, 1030, 12, 250, "f32"),    # 1, 2, 4 chunks
+    (3, 101, 5, 1000, "f32"), (2, 36, 48, 513, "f32"), (6, 4, 64, 300, "bf16"),         # 16
+    (40, 600, 60, 130, "bf16"), (23, 1500, 16, 301, "bf16"), (50, 2035, 7, 83, "bf16"),
+    (1, 64, 12, 16 * 1024 + 9, "f32"), (2, 72, 17, 8192 + 256, "bf16"),                 # segments
+    (64, 512, 16, 96, "f32"), (70, 512, 32, 80, "bf16"), (3, 520, 64, 100, "f32"),
+    (20, 512, 64, 130, "f32"), (16, 1024, 16, 1024, "bf16"),       # named plans: u not aligned
+]
+
+
+@pytest.mark.parametrize("case", NOT_FINITE, ids=lambda c: "B%d_D%d_d%d_T%d_%s" % c)
+def test_inputs_that_are_not_finite(case):
+    """Inputs that are not finite, and (float32) one that only its nearest bfloat16 is
+    not: each affects its row and channel from its own step on, as in the recurrence.
+    Everything before, and every other row and channel, is what the call with zeros in
+    their place gives: the same bits elsewhere, within the tolerance of _same in the
+    row itself.  From there on the VALU scan's values, finite where those are."""
+    import torch
+
+    import paper_2310_18780_amd as lh
+
+    B, D, d, T, io = case
+    assert lh.prefill_path(B, D, d, T, io=io)[0] == "mfma"
+    _, t, u = _inputs(*case, seed=B * 1000 + d)
+    if lh.prefill_plan(B, D, d, T, io=io) != "scan":
+        u = torch.cat([u.flatten(), u.flatten()[:1]])[1:].view(u.shape)
+        assert u.data_ptr() % 16 != 0
+    args = (t["lam"], t["R"] / 256, t["h0"] / 256)  # no sum of outputs near the largest float32
+    values = [float("inf"), float("-inf"), float("nan")] + ([3.399e38, -3.399e38] if io == "f32" else [])
+    spots = {}
+    for i, v in enumerate(values * 3):  # first, last and other steps, rows and channels
+        spots[((i * 7) % B if i else B - 1, (i * 37 + D - 1) % D)] = (
+            (T - 1 if i == 0 else 0 if i == 1 else (i * 53 + 5) % T), v)
+    for (b, c), (s, v) in spots.items():
+        u[b, s, c] = 0
+    print(f"[not finite] {case} {spots}", flush=True)
+    clean = _run(lambda x, y: lh.prefill(*args, u, x, y), u, d)
+    for (b, c), (s, v) in spots.items():
+        u[b, s, c] = v
+    auto = _run(lambda x, y: lh.prefill(*args, u, x, y), u, d)
+    scan = _run(lambda x, y: lh.prefill_with_plan(*args, u, x, y, T), u, d)
+    hit = torch.zeros((B, D), dtype=torch.bool, device="cuda")
+    for (b, c), (s, v) in spots.items():
+        hit[b, c] = True
+        ya, yc, ys = (r[0][b, :, c].float() for r in (auto, clean, scan))
+        tol = 2 * REL_TOL * yc.abs().max() + 2 * BF16_REL * yc.abs() * (io == "bf16")
+        assert bool(((ya - yc).abs()[:s] <= tol[:s]).all()), (b, c, s, v)
+        assert torch.equal(torch.isfinite(ya), torch.isfinite(ys)), (b, c, s, v)
+        assert ya[s] == ys[s] or (ya[s] != ya[s] and ys[s] != ys[s]), (b, c, s, v)
+        ok = torch.isfinite(ys)
+        ok[:s] = False
+        if bool(ok.any()):
+            assert bool(((ya - ys).abs()[ok] <= 2 * REL_TOL * ys[ok].abs().max()).all()), (b, c, s, v)
+        xa, xs = auto[1][b, c], scan[1][b, c]
+        assert torch.equal(torch.isfinite(xa.abs()), torch.isfinite(xs.abs())), (b, c, s, v)
+    assert torch.equal(auto[0].transpose(1, 2)[~hit], clean[0].transpose(1, 2)[~hit])
+    assert torch.equal(auto[1][~hit], clean[1][~hit])
