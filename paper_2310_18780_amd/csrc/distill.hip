@@ -49,6 +49,8 @@
 //
 // Both finalise the gradients without dividing by lambda, so A = 0 is exact.  The
 // traffic is the target read once.
+#include <float.h>
+
 #include <type_traits>
 
 #include "lh_internal.hpp"
@@ -277,9 +279,9 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
     // tables, lane = mode: wave 0 lambda^b, wave 1 lambda^(16 alpha), wave 2
     // lambda^(256 k) (in the loop), float64 products rounded once
     double lr = 0.0, li = 0.0;  // lambda^(1, 16 or 256)
+    double sn = 0.0, cs = 0.0;  // (wave 0 needs them again at the end)
     if (w < 3 && lane < d) {
         const double a = Ac[lane], th = Tc[lane];
-        double sn, cs;
         sincos(th, &sn, &cs);
         lr = a * cs;
         li = a * sn;
@@ -318,20 +320,24 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
 #pragma unroll
     for (int m = 0; m < DM; ++m)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) P1[m][i] = p16[16 * m + q][(4 * i + g + 15) % 16];
+        for (int i = 0; i < 4; ++i) {
+            P1[m][i] = p16[16 * m + q][(4 * i + g + 15) % 16];
+            // lambda^240 meets zeros in the first tile, also where it overflows (and all
+            // taps it would count for, past the 256th, do too)
+            if (i == 0 && g == 0)
+                P1[m][i] = make_float2(fminf(fmaxf(P1[m][i].x, -FLT_MAX), FLT_MAX),
+                                       fminf(fmaxf(P1[m][i].y, -FLT_MAX), FLT_MAX));
+        }
     f32x4 F[DM][4];  // Re F1, Im F1, Re F', Im F': rows modes 16 m + 4 g + i, column b = q
 #pragma unroll
     for (int m = 0; m < DM; ++m)
 #pragma unroll
         for (int z = 0; z < 4; ++z) F[m][z] = f32x4{0.f, 0.f, 0.f, 0.f};
     float lacc = 0.f;
-    // Rows of a tile that take part in F: not a = 0 (added at the end), and not those
-    // past the last tap, whose powers may overflow where |lambda| > 1 while every
-    // power up to lambda^(L-1) is finite (inf times the zero errors there is no zero).
-    auto inside = [&](int64_t s0, int i) {
-        const int64_t s = s0 + 16 * (4 * i + g);
-        return s > 0 && s < L;
-    };
+    // Rows of the last tile that take part in F: not those past the last tap, whose
+    // powers may overflow where |lambda| > 1 while every power up to lambda^(L-1) is
+    // finite (inf times the zero errors there is no zero).
+    auto inside = [&](int64_t s0, int i) { return 16 * (4 * i + g) < int(L - s0); };
 
     for (int64_t k0 = 0; k0 < ntile; k0 += kMaxTiles) {
         const int nk = int(ntile - k0 < kMaxTiles ? ntile - k0 : kMaxTiles);
@@ -386,41 +392,52 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
                     }
                 }
             };
-            if (s0 == 0 || s0 + kTile > L)  // (in every tile the masks take 1 of the 30 us)
+            if (s0 + kTile > L)  // (in every tile the masks take 1 of the 30 us)
                 accumulate(std::true_type{});
             else
                 accumulate(std::false_type{});
         }
     }
 
-    // F = lambda^16 F1 + e[0], sums over b, then over the waves; powers that no tap
-    // has stay out here too
+    // F = lambda^16 F1 + e[0], sums over b, then over the waves; for at most 16 taps
+    // (only a = 0) powers that no tap has stay out here too
     __syncthreads();
     const float e0 = w == 0 ? e0_s[q] : 0.f;
     const float fb = float(q);
-    const float2 none = make_float2(0.f, 0.f);
-    const bool rows = L > 16;  // any a > 0
+    auto finish = [&](auto few) {
+        constexpr bool FEW = decltype(few)::value;
+        const float2 none = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int m = 0; m < DM; ++m)
+        for (int m = 0; m < DM; ++m)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int n = 16 * m + 4 * g + i;
-            const float2 p = q < L ? pw[n][q] : none;               // lambda^b
-            const float2 pb = q > 0 && q < L ? pw[n][q - 1] : none;  // lambda^(b-1)
-            float2 f = rows ? cmul(p16[n][1], make_float2(F[m][0][i], F[m][1][i])) : none;
-            f.x += e0;
-            const float2 fd = rows ? cmul(pw[n][15], make_float2(F[m][2][i], F[m][3][i])) : none;
-            const float2 gv = cmul(p, f);
-            const float2 s1 = cmul(p, fd), s2 = cmul(pb, f);
-            const float v0 = row_sum16(gv.x), v1 = row_sum16(gv.y);
-            const float v2 = row_sum16(fmaf(fb, s2.x, s1.x)), v3 = row_sum16(fmaf(fb, s2.y, s1.y));
-            if (q == 0) {
-                red[w][n][0] = v0;
-                red[w][n][1] = v1;
-                red[w][n][2] = v2;
-                red[w][n][3] = v3;
+            for (int i = 0; i < 4; ++i) {
+                const int n = 16 * m + 4 * g + i;
+                float2 p = pw[n][q];                       // lambda^b
+                float2 pb = q > 0 ? pw[n][q - 1] : none;  // lambda^(b-1)
+                float2 f = none, fd = none;
+                if constexpr (FEW) {
+                    if (q >= L) p = pb = none;
+                } else {
+                    f = cmul(p16[n][1], make_float2(F[m][0][i], F[m][1][i]));
+                    fd = cmul(pw[n][15], make_float2(F[m][2][i], F[m][3][i]));
+                }
+                f.x += e0;
+                const float2 gv = cmul(p, f);
+                const float2 s1 = cmul(p, fd), s2 = cmul(pb, f);
+                const float v0 = row_sum16(gv.x), v1 = row_sum16(gv.y);
+                const float v2 = row_sum16(fmaf(fb, s2.x, s1.x)), v3 = row_sum16(fmaf(fb, s2.y, s1.y));
+                if (q == 0) {
+                    red[w][n][0] = v0;
+                    red[w][n][1] = v1;
+                    red[w][n][2] = v2;
+                    red[w][n][3] = v3;
+                }
             }
-        }
+    };
+    if (L > 16)
+        finish(std::false_type{});
+    else
+        finish(std::true_type{});
     const float lw = wave_sum64(lacc);
     if (lane == 0) loss_s[w] = lw;
     __syncthreads();
@@ -434,9 +451,7 @@ __global__ __launch_bounds__(kThreads) void distill_mfma_kernel(
         for (int z = 0; z < 4; ++z)
             v[z] = (double(red[0][tid][z]) + red[1][tid][z]) + (double(red[2][tid][z]) + red[3][tid][z]);
         const float2 r = Rc[tid];
-        const double a = Ac[tid], th = Tc[tid];
-        double sn, cs;
-        sincos(th, &sn, &cs);
+        const double a = Ac[tid];
         const double rx = double(r.x) * v[2] - double(r.y) * v[3];
         const double ry = double(r.x) * v[3] + double(r.y) * v[2];
         dR[int64_t(c) * d + tid] = make_float2(float(2.0 * v[0]), float(-2.0 * v[1]));
