@@ -23,7 +23,12 @@
 // does, else 2: small states are latency-bound, and more wavefronts with
 // fewer rows each finish sooner (B = 16, D = 768, d = 16: 1.95 us per step
 // with NB = 2 against 2.51 us with NB = 8; B = 64, D = 2048: 6.0 us with
-// NB = 8 against 6.3 us with NB = 4).  A workgroup is one wavefront
+// NB = 8 against 6.3 us with NB = 4).  NB = 1 where pairs of rows leave at most 512
+// wavefronts (B = 4, D = 512, d = 17: 2.40 us against 2.69 us) and for a single
+// row, and no larger NB than the rows need (B = 2, D = 4096, d = 33: 3.85 us with 2,
+// 5.23 us with 8, six of them idle).  Up to 32 single modes (8-byte accesses) take at most
+// 2 rows while the state is small (kFewRowsBytes; B = 64, D = 2048, d = 5: 5.51 us
+// against 5.90 us with 8; d = 9, 9.4 MB: 8.71 and 7.52 us).  A workgroup is one wavefront
 // (64 / LPR channels x NB batch rows) up to LPR = 16; with LPR >= 32 (two
 // channels or fewer per wavefront) it is four wavefronts, so that
 // a workgroup covers 8 channels (B = 256, D = 2048, d = 64: 71 us per step
@@ -49,8 +54,14 @@
 // of every batch row of the state, and whole 128-byte lines of u_t and y_t
 // stay with one L2.
 //
-// Generic path (larger d, or a grid past its limits): lanes take single modes j, j +
-// LPR, ... (LPR = next power of two >= d, <= 64) or pairs, one batch row per thread.
+// Generic path (larger d, a grid past its limits, or 1 < d <= 16 in single modes on a
+// state of at most kStridedBytes): lanes take single modes j, j + LPR, ... (LPR = next
+// power of two >= d, <= 64) or pairs, one batch row per thread.  Its four-wavefront
+// workgroups step such small states in 0.8-0.95 of the lanes path's time, layers
+// replayed from a graph (B = 128, D = 512: d = 5 3.68 us against 4.65 us, d = 7 3.82
+// against 4.74; B = 32, D = 1024, d = 15, 3.9 MB: 3.87 against 4.82); from about 4.5 MB
+// on the lanes path with two rows per thread is level or faster (B = 128, D = 512, d =
+// 9, 4.7 MB: 5.43 us against 5.52 us).
 #include "lh_internal.hpp"
 
 namespace lh {
@@ -64,6 +75,8 @@ constexpr int kXcds = 8;
 constexpr int kMaxRowsPerThread = 8;
 constexpr int64_t kMinWaves = 2048;  // wavefronts the row count per thread is chosen for
 constexpr int64_t kStreamStateBytes = INT64_C(16) << 20;  // non-temporal state loads up to this size
+constexpr int64_t kFewRowsBytes = INT64_C(8) << 20;  // single modes, d <= 32: at most two rows per thread up to this size
+constexpr int64_t kStridedBytes = INT64_C(4) << 20;  // single modes, 1 < d <= 16: the generic path up to this size
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
@@ -279,12 +292,14 @@ __global__ __launch_bounds__(kBlock) void step_generic_kernel(
 }
 
 // Batch rows per thread of the lanes path (see the file comment).
-int pairs_rows_per_thread(int lpr, int64_t B, int64_t D)
+int pairs_rows_per_thread(int lpr, int vec, int64_t B, int64_t D, int64_t d)
 {
     const int64_t waves_per_group = (D * lpr + 63) / 64;
-    for (int nb = kMaxRowsPerThread; nb > 2; nb /= 2)
-        if ((B + nb - 1) / nb * waves_per_group >= kMinWaves) return nb;
-    return 2;
+    auto waves = [&](int nb) { return (B + nb - 1) / nb * waves_per_group; };
+    const int most = vec == 1 && d <= 32 && 8 * B * D * d <= kFewRowsBytes ? 2 : kMaxRowsPerThread;
+    for (int nb = most; nb > 2; nb /= 2)
+        if (nb / 2 < B && waves(nb) >= kMinWaves) return nb;
+    return B > 1 && waves(2) > kMinWaves / 4 ? 2 : 1;
 }
 
 // 2-D grid of the lanes path; false when it does not fit the grid limits
@@ -327,6 +342,7 @@ hipError_t launch_nb(int nb, const Step& s)
         LH_NB(8)
         LH_NB(4)
         LH_NB(2)
+        LH_NB(1)
         default: return hipErrorInvalidValue;
     }
 #undef LH_NB
@@ -409,8 +425,9 @@ hipError_t launch_step(const float2* lam, const float2* R, const float* h0, floa
     const int vec = d % 2 == 0 && aligned16 ? 2 : 1;
     int fast_lpr = 1;
     while (int64_t(fast_lpr) * vec < d) fast_lpr *= 2;
-    if (fast_lpr <= 64 && B < (INT64_C(1) << 31) && D < (INT64_C(1) << 31)) {
-        const int nb = pairs_rows_per_thread(fast_lpr, B, D);
+    const bool small_odd = vec == 1 && d > 1 && d <= 16 && 8 * B * D * d <= kStridedBytes;
+    if (fast_lpr <= 64 && !small_odd && B < (INT64_C(1) << 31) && D < (INT64_C(1) << 31)) {
+        const int nb = pairs_rows_per_thread(fast_lpr, vec, B, D, d);
         Step s{lam, R, h0, state, u_t, y_t, int(B), int(D), int(d), dim3(), 0, stream};
         if (pairs_grid(fast_lpr, nb, B, D, &s.grid, &s.ntiles)) {
             const bool ntl = 8 * B * D * d <= kStreamStateBytes;
