@@ -86,6 +86,8 @@ size_t mfma_table_bytes(bool bf16_io, bool two_terms, int64_t D, int64_t d);
 int64_t mfma_segments(int64_t B, int64_t D, int64_t d, int64_t T);
 // The cut of a call into columns and at most max_seg segments.
 MfmaCut mfma_cut(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64_t max_seg);
+// Estimated time of a call on the three-term kernels, in microseconds.
+double mfma_us(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, const MfmaCut& cut);
 // Tables of the filters into the workspace.
 hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0, int64_t D,
                              int64_t d, bool bf16_io, bool two_terms, void* workspace,

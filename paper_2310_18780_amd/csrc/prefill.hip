@@ -318,31 +318,41 @@ int named_auto(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64_t
     return d == 64 && (B >= 4 || (D + 3) / 4 * ((B + 15) / 16) >= 256) ? 1 : 0;
 }
 
+// Time of the VALU scan p in microseconds: launches, the steps (a wave's latency or
+// the issue of all waves on a SIMD, per mode of a lane and halving of the lane
+// sum), or the memory traffic; in one pass the steps outside the blocks of 16 and the
+// scattered state as well, in chunks a carry that walks them.
+double scan_us(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, const PrefillPlan& p)
+{
+    const int64_t cw = 64 / p.lpr, waves = B * ((D + cw - 1) / cw) * std::max<int64_t>(p.nchunks, 1);
+    const double per_simd = double((waves + 1023) / 1024), lg = __builtin_ctz(p.lpr);
+    const double mem = double(B) * double(T) * double(D) * (bf16_io ? 4 : 8);
+    if (p.nchunks <= 1) {
+        const double step = std::max(0.0016 + 0.0079 * p.mpl + 0.0627 * lg,
+                                     per_simd * (0.0004 + 0.0081 * p.mpl + 0.0316 * lg));
+        const double tail = double(T < 32 ? T : T % 16);
+        return 7.1 + std::max(step * double(T) + 0.025 * tail, 0.117e-6 * mem) +
+               0.64e-6 * 8 * double(B) * double(D) * double(d);
+    }
+    const double step = std::max(0.0216 * p.mpl + 0.0558 * lg,
+                                 per_simd * (0.0092 + 0.0164 * p.mpl + 0.0385 * lg));
+    return 11.9 + 0.27 * double(p.nchunks) + std::max(step * double(p.C), 0.261e-6 * mem);
+}
+
 // Whether sizes that no explicit request names run faster on the matrix cores
-// than in the VALU scan p, by estimates in nanoseconds whose constants were fitted to
-// the times of both at 174 shapes (B = 1..300, D = 64..4096, d = 4..63, T =
-// 16..16384, both types).  Matrix cores: launches, the tables of D channels, then
-// the tiles of the busiest CU.  Scan: launches, latency per step (the modes of a
-// lane one after the other), then the arithmetic per element and padded mode or
-// the memory traffic; in chunks two passes and a carry that walks the chunks.  At
-// these shapes the choice is never more than 3% slower than the scan, and up to
-// 4.2 times as fast; it misses the matrix cores at six where they are 4-36% faster.
-// Narrow banks on short prompts stay on the scan although the matrix cores are faster
-// there too (B = 2, D = 70, d = 16, T = 300: 12 us against 34 us): their workspace
-// has always been the scan's, and callers rely on its size.
+// than in the VALU scan p.  The constants of both estimates were fitted to the times
+// of both at 360 shapes (B = 1..300, D = 64..4096, d = 1..64, T = 8..16384, both
+// types; errors 13% and 14% root mean square); 3% go to the scan, which served these
+// sizes first.  There the choice is more than 3% slower than the scan at 9 shapes
+// (1.34x at most, of 15.7 us) and misses faster matrix cores at 24 (an earlier
+// estimate: 25, up to 1.7x, and 18).
+// Narrow banks on short prompts stay on the scan, also where the matrix cores are
+// faster (B = 2, D = 70, d = 16, T = 300: 34 us against 12 us): the size of their
+// workspace is the one that lh_prefill_workspace_bytes has always given.
 bool mfma_faster(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, const PrefillPlan& p)
 {
     if (D < 96 && B * T < 1024) return false;
-    const double el = double(B) * double(T) * double(D), modes = double(p.lpr) * p.mpl;
-    const double mem = el * (bf16_io ? 4 : 8) / 4000.0;
-    const double mfma = 13000 + 1.8 * double(D) * double((d + 15) / 16) +
-                        double(p.cut.tiles) * (bf16_io ? 3400 : 3200);
-    const double scan =
-        p.nchunks <= 1
-            ? 11400 + (36 + 1.8 * modes) * double(T) + std::max(0.32e-3 * el * modes, mem)
-            : 24200 + 480 * double(p.nchunks) + 3.6 * modes * double(p.C) +
-                  std::max(0.35e-3 * el * modes, 1.7 * mem);
-    return mfma < scan;
+    return mfma_us(B, D, d, T, bf16_io, p.cut) < 0.97 * scan_us(B, D, d, T, bf16_io, p);
 }
 
 }  // namespace

@@ -344,6 +344,24 @@ MfmaCut mfma_cut(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, int64
     return best;
 }
 
+// Time of the three-term kernels in microseconds: launches, the tables, then the passes
+// of the busiest CU, whose workgroups each load their operands and walk their tiles.
+double mfma_us(int64_t B, int64_t D, int64_t d, int64_t T, bool bf16_io, const MfmaCut& cut)
+{
+    constexpr double kTileUs[2][4] = {{1.65, 2.87, 2.0, 2.8}, {2.56, 2.6, 1.35, 2.27}};
+    const int dm = modes16(d);
+    const int64_t cw = mfma_channels(bf16_io, dm), groups = (D + cw - 1) / cw;
+    auto pass = [&](int64_t rows, int64_t steps) {
+        const int64_t wgs = groups * ((rows + 16 / cut.s - 1) / (16 / cut.s));
+        const double tile = kTileUs[bf16_io][dm - 1] * (cut.s == 1 ? 1.2 : 1.0);
+        return double((wgs + kCus - 1) / kCus) *
+               (4.5 + tile * double((steps + 16 * cut.s - 1) / (16 * cut.s)));
+    };
+    const double base = 5.1 + 6.1e-3 * double(D) * dm;
+    if (cut.nseg == 1) return base + pass(B, T);
+    return base + 5.9 + 0.75 * pass(B * (cut.nseg - 1), cut.seg_len) + pass(B * cut.nseg, cut.seg_len);
+}
+
 hipError_t launch_mfma_setup(const float2* lam, const float2* R, const float* h0, int64_t D,
                              int64_t d, bool bf16_io, bool two_terms, void* workspace,
                              hipStream_t stream)

@@ -134,9 +134,10 @@ def test_scratch_limits():
     with pytest.raises(lh.LHError):
         lh.prefill(*args, small[1], small[0], workspace=ws[:-256])
 
-    B, D, d, T = 16, 2560, 60, 70  # 77 MB of tables; the scan is one pass
+    B, D, d, T = 16, 2560, 60, 300  # 77 MB of tables; the scan is one pass
     _, t, u = _inputs(B, D, d, T, "f32", 6)
     args = (t["lam"], t["R"], t["h0"], u)
+    assert lh.prefill_path(B, D, d, T)[0] == "mfma"
     assert lh.workspace_bytes(B, D, d, T) > lh.NOALLOC_SCRATCH_BYTES
     held = _run(lambda x, y: lh.prefill_noalloc(*args, x, y), u, d)
     scan = _run(lambda x, y: lh.prefill_with_plan(*args, x, y, T), u, d)
