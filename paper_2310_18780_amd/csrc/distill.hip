@@ -27,11 +27,12 @@
 // register i).  The powers of a tile are lambda^(16 alpha) (constant) times
 // lambda^(256 k), both from float64 products rounded once, so that no rounding error
 // builds up along t.  A workgroup of four waves per channel, each wave every fourth
-// tile.  D = 2048, d = 16, L = 4096: 65 -> 30 us (the VALU kernel below issues 23
+// tile.  D = 2048, d = 16, L = 4096: 65 -> 28 us (the VALU kernel below issues 23
 // instructions per (t, n)), D = 2048, d = 60, L = 1024: 216 -> 49 us, D = 256, d = 16,
-// L = 4096: 21 -> 9 us.  Of the 30 us the float32 matrix products are 10 us (24 of 32
-// cycles per tile and wave), 10 us the latency of loads and tables before the first
-// tile in two rounds of workgroups; more wavefronts per SIMD spill (34-50 us).
+// L = 4096: 21 -> 9 us.  Of the 28 us the float32 matrix products are 10 us (24 of 32
+// cycles per tile and wave; the counters show the matrix units busy for 0.30 of the time
+// and vector instructions issued for 0.46), 10 us the latency of loads and tables before
+// the first tile in two rounds of workgroups; more wavefronts per SIMD spill (34-50 us).
 //
 // d > 64: on the VALU (distill_kernel).  One workgroup of 256 threads per channel.
 // The time axis is cut into segments of 256 x 16 steps; in a segment thread k owns 16

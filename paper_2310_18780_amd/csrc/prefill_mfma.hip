@@ -53,27 +53,32 @@
 // 16 steps with the same sign).  d is padded to a multiple of 16 with
 // modes of zero operands.
 //
-// What bounds it.  The instruction issue: a tile (256 (row, step) cells of a
-// workgroup's channels) takes 2 to 3 us, of which vector and matrix instructions
-// issue for about three quarters (counters of the [64, 4096, 2048] bfloat16
-// prefill), next to the movement of u and y, whose rate depends on how much of it
+// What bounds it.  No unit is full: a tile (256 (row, step) cells of a workgroup's
+// channels) takes 2 to 3 us, of which the matrix units are busy for 0.19 (bfloat16 d =
+// 16; float32 d = 32 0.24, d = 64 0.27; 16 cycles per product) and vector
+// instructions issue for 0.31 to 0.33 (4 cycles each, by the counters of the three
+// prefills); the two waves of a SIMD wait for 0.4 of their time, for operands from LDS
+// and for each other at the tile's barrier, S > 1 also for the walk.  Beside it the
+// movement of u and y, whose rate depends on how much of it
 // is in flight, in the opposite sense of a plain copy: moved without arithmetic
-// in 64-byte pieces of lines that lie D elements apart, that prompt takes 0.43 ms
-// (5.0 TB/s; a contiguous copy of these bytes 0.45 ms) with 8 KiB of loads in
-// flight per workgroup and CU, 0.60-0.65 ms with 16 KiB, 0.71-0.77 ms with 32
+// in 64-byte pieces of lines that lie D elements apart, the [64, 4096, 2048] bfloat16
+// prompt takes 0.43 ms (5.0 TB/s; a contiguous copy of these bytes 0.45 ms) with 8 KiB
+// of loads in flight per workgroup and CU, 0.60-0.65 ms with 16 KiB, 0.71-0.77 ms with 32
 // KiB; 32-byte pieces take 0.54-0.61 ms.  Hence
-//   - chunks of 16 steps: the A operands of a channel are 7 KiB (bfloat16, d <= 16)
-//     to 30 KiB (float32, d = 64), half of what chunks of 32 steps need, so that a
+//   - chunks of 16 steps: the A operands of a channel are 7 KiB (bfloat16, d <= 16,
+//     two terms) to 30 KiB (d = 64), half of what chunks of 32 steps need, so that a
 //     wave holds up to four channels and moves pieces of up to 64 bytes;
 //   - loads a tile ahead in two halves, staged as they arrive;
 //   - independent chains of products issued in turn, lambda^C and its correction
 //     read from LDS, the tile loop free of any other path.
 // Against chunks of 32 steps in 16- to 32-byte pieces (and, for few rows, one pass
-// for segment states more; for other d or D the VALU scan), same box: [16, 2048,
-// 768] float32 d = 16 165 -> 77 us; [4, 65536, 1024] float32 d = 32 983 -> 781 us;
-// [64, 2048, 2048] float32 d = 32 752 -> 656 us; [256, 1024, 2048] float32 d = 64
-// 2327 -> 2130 us; [64, 4096, 2048] bfloat16 d = 16 666 -> 648 us; [7, 1999, 1000]
-// bfloat16 d = 12 (VALU) 115 -> 34 us.  Also measured: the pairs' loads issued
+// for segment states more; for other d or D the VALU scan): [16, 2048, 768] float32
+// d = 16 167 -> 74 us; [4, 65536, 1024] float32 d = 32 938 -> 690 us; [256, 1024, 2048]
+// float32 d = 64 2280 -> 2180 us; [64, 4096, 2048] bfloat16 d = 16 601 -> 583 us; [7,
+// 1999, 1000] bfloat16 d = 12 (VALU) 112 -> 34 us.  Slower than they were are some
+// batches of 50 to 120 rows with bfloat16 u and y, whose wider channel groups fill
+// the last round of CUs worse ([59, 256, 2272] d = 32 95 -> 119 us, [117, 512, 256] 39 -> 46
+// us).  Also measured: the pairs' loads issued
 // half a tile ahead 1.04-1.15x the time, one at a time with a forced wait between
 // the halves 1.02-1.5x, outputs stored at the tile's start 1.05-1.16x, scalar-base
 // addresses for the stores 1.1-1.2x.
