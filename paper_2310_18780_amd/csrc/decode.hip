@@ -23,9 +23,10 @@
 // does, else 2: small states are latency-bound, and more wavefronts with
 // fewer rows each finish sooner (B = 16, D = 768, d = 16: 1.95 us per step
 // with NB = 2 against 2.51 us with NB = 8; B = 64, D = 2048: 6.0 us with
-// NB = 8 against 6.3 us with NB = 4).  NB = 1 where pairs of rows leave at most 512
-// wavefronts (B = 4, D = 512, d = 17: 2.40 us against 2.69 us) and for a single
-// row, and no larger NB than the rows need (B = 2, D = 4096, d = 33: 3.85 us with 2,
+// NB = 8 against 6.3 us with NB = 4).  NB = 1 where pairs of rows leave fewer than 512
+// wavefronts (B = 4, D = 512, d = 24: 2.50 us against 2.73 us; at 512, B = 4, D = 1024, d =
+// 32: 2.65 against 2.56 us), with LPR >= 32 not more than 512 (B = 4, D = 512, d = 17: 2.40
+// us against 2.69 us), and for a single row, and no larger NB than the rows need (B = 2, D = 4096, d = 33: 3.85 us with 2,
 // 5.23 us with 8, six of them idle).  Up to 32 single modes (8-byte accesses) take at most
 // 2 rows while the state is small (kFewRowsBytes; B = 64, D = 2048, d = 5: 5.51 us
 // against 5.90 us with 8; d = 9, 9.4 MB: 8.71 and 7.52 us).  A workgroup is one wavefront
@@ -299,7 +300,7 @@ int pairs_rows_per_thread(int lpr, int vec, int64_t B, int64_t D, int64_t d)
     const int most = vec == 1 && d <= 32 && 8 * B * D * d <= kFewRowsBytes ? 2 : kMaxRowsPerThread;
     for (int nb = most; nb > 2; nb /= 2)
         if (nb / 2 < B && waves(nb) >= kMinWaves) return nb;
-    return B > 1 && waves(2) > kMinWaves / 4 ? 2 : 1;
+    return B > 1 && waves(2) >= kMinWaves / 4 + (lpr >= 32) ? 2 : 1;
 }
 
 // 2-D grid of the lanes path; false when it does not fit the grid limits
