@@ -110,3 +110,15 @@ def test_multihead_step(d, shift):
     ref_x = l64 * x0 + z[..., None]
     bound = 5 * EPS * (2 ** 0.5 * l64.abs() * x0.abs() + z.abs()[..., None])
     assert bool(((x.to(torch.complex128) - ref_x).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("B,D,d,shift", [
+    (5, 4096, 33, 0),                     # eight rows per thread, three of them past the batch
+    (2, 4096, 33, 0), (3, 4096, 17, 0),   # no more rows than there are; two at most in single modes
+    (5, 1024, 24, 0), (4, 1024, 32, 0),   # one and two rows: 384 and 512 wavefronts of pairs
+    (63, 2048, 9, 0),                     # single modes past the small states: eight rows
+    (33, 1024, 15, 0), (35, 1024, 15, 0),  # the generic path up to 4 MiB, the lanes past it
+    (35, 1024, 16, 1), (9, 2048, 1, 0),
+])
+def test_rows_per_thread(B, D, d, shift):
+    test_step(d, B, D, "f32", shift)
