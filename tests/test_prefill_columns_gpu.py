@@ -319,3 +319,30 @@ def test_inputs_that_are_not_finite(case):
         assert torch.equal(torch.isfinite(xa.abs()), torch.isfinite(xs.abs())), (b, c, s, v)
     assert torch.equal(auto[0].transpose(1, 2)[~hit], clean[0].transpose(1, 2)[~hit])
     assert torch.equal(auto[1][~hit], clean[1][~hit])
+
+
+@pytest.mark.parametrize("case", [
+    (1, 64, 16, 4096, "bf16", 16, 8), (1, 64, 16, 4096, "f32", 16, 8),   # segments
+    (20, 512, 64, 130, "f32", 2, 1), (59, 2272, 32, 256, "bf16", 2, 1),
+], ids=lambda c: "B%d_D%d_d%d_T%d_%s" % c[:5])
+def test_unaligned_named_plans(case):
+    """The automatic call at sizes of the named plans with u and y one element past a
+    16-byte boundary, where it takes the three-term kernel and its larger tables in
+    the same workspace, against the VALU scan."""
+    import torch
+
+    import paper_2310_18780_amd as lh
+
+    B, D, d, T, io, *cut = case
+    assert lh.prefill_plan(B, D, d, T, io=io) != "scan"
+    assert lh.prefill_path(B, D, d, T, io=io) == ("mfma", *cut)
+    _, t, u = _inputs(*case[:5], seed=B * 1000 + d)
+    shift = lambda a: torch.cat([a.flatten()[:1], a.flatten()])[1:].view(a.shape)  # noqa: E731
+    u = shift(u)
+    print(f"[unaligned] {case}", flush=True)
+    args = (t["lam"], t["R"], t["h0"], u)
+    y, x = shift(torch.full_like(u, float("nan"))), torch.empty((B, D, d), dtype=torch.complex64, device="cuda")
+    assert u.data_ptr() % 16 and y.data_ptr() % 16
+    lh.prefill(*args, x, y)
+    scan = _run(lambda x, y: lh.prefill_with_plan(*args, x, y, T), u, d)
+    _same((y, x), scan, io)
